@@ -10,7 +10,10 @@
 namespace gockpt {
 
 constexpr int kBlock = 256;             // threads per block, 4 wavefronts
+constexpr int kFusedBlock = 64;         // threads per block of the fused kernel, one wavefront
 constexpr int kFusedWideBlock = 1024;   // the fused kernel's optional wide block, 16 wavefronts
+constexpr int kWaveSlots = 256 * 32;     // wavefronts the device holds at once
+constexpr unsigned kFusedLds = 13312;   // LDS of a fused block under the residency limit: 12 blocks a compute unit
 constexpr int kVec = 8;                 // elements per thread per group
 constexpr int kPrepassMaxBlocks = 2048; // partial sums slots
 constexpr int kFinalizeThreads = 256;
@@ -87,7 +90,7 @@ struct PackPlan {
     uint8_t* ring;
     uint64_t ring_bytes;
     int32_t ring_nt;      // 1: nontemporal ring stores
-    int32_t pad;
+    int32_t any;          // 0: the step packs nothing (the ranges above are empty)
 };
 
 struct FusedArgs {
@@ -102,7 +105,7 @@ struct FusedArgs {
     int32_t quads_per_thread;       // 1, 2 or 4 quads (4 elements) per thread
     int32_t grad_kind;              // kGradBF16 or kGradFP16
     int32_t nt;                     // nontemporal state loads and stores
-    int32_t block;                  // threads per block: kBlock or kFusedWideBlock (one quad per lane)
+    int32_t block;                  // threads per block: kFusedBlock or kFusedWideBlock (one quad per lane)
     PackPlan pack;
 };
 
@@ -112,7 +115,7 @@ struct Knobs {
     int ring_nt;      // nontemporal ring stores
     int prepass_nt;   // nontemporal gradient loads in the prepass
     int fused_nt;     // nontemporal loads and stores of the state in the fused kernel
-    int fused_block;  // fused kernel threads per block: kBlock (default) or kFusedWideBlock
+    int fused_block;  // fused kernel threads per block: kFusedBlock (default) or kFusedWideBlock
 };
 
 // What the finalize of one step needs besides the partials.

@@ -44,15 +44,6 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32x4 ld_u32x4(const void* p) {
     return *reinterpret_cast<const u32x4*>(p);
 }
-__device__ __forceinline__ f32x4 ld_f32x4(const float* p) {
-    return *reinterpret_cast<const f32x4*>(p);
-}
-__device__ __forceinline__ void st_f32x4(float* p, f32x4 v) {
-    *reinterpret_cast<f32x4*>(p) = v;
-}
-__device__ __forceinline__ void st_u32x4(void* p, u32x4 v) {
-    *reinterpret_cast<u32x4*>(p) = v;
-}
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -84,12 +75,6 @@ __device__ __forceinline__ void ring_st16(const PackPlan& pk, uint64_t off, u32x
         __builtin_nontemporal_store(v, dst);
     else
         *dst = v;
-}
-__device__ __forceinline__ void ring_st_f32x8(const PackPlan& pk, uint64_t off, f32x4 lo, f32x4 hi) {
-    u32x4 a = __builtin_bit_cast(u32x4, lo);
-    u32x4 b = __builtin_bit_cast(u32x4, hi);
-    ring_st16(pk, off, a);
-    ring_st16(pk, off + 16, b);
 }
 __device__ __forceinline__ void ring_st_u16(const PackPlan& pk, uint64_t off, uint16_t v) {
     if (off >= pk.ring_bytes) off -= pk.ring_bytes;
@@ -395,14 +380,105 @@ __device__ __forceinline__ void ring_st_f32x4(const PackPlan& pk, uint64_t off, 
     ring_st16(pk, off, __builtin_bit_cast(u32x4, v));
 }
 
+// Where a tile of kTile elements from element i0 meets the ends of the
+// arrays and of the pack ranges: offsets inside the tile, the same for every
+// lane of the block (they stay in scalar registers).
+struct TileSpan {
+    uint32_t g_end;     // gradients below it are packed
+    uint32_t c_beg;     // state from it on may be packed...
+    uint32_t s_end[3];  // ...up to here, per state array
+};
+
+template <uint32_t kTile>
+__device__ __forceinline__ uint32_t tile_cut(int64_t x, int64_t i0) {
+    const int64_t d = x - i0;
+    return d <= 0 ? 0u : (d >= static_cast<int64_t>(kTile) ? kTile : static_cast<uint32_t>(d));
+}
+
+template <uint32_t kTile>
+__device__ __forceinline__ TileSpan tile_span(const FusedArgs& a, int64_t i0, int skip) {
+    TileSpan t;
+    t.g_end = skip ? 0u : tile_cut<kTile>(a.pack.g_end, i0);  // a skipped step's gradients are never replayed
+    t.c_beg = tile_cut<kTile>(a.pack.cb, i0);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) t.s_end[k] = tile_cut<kTile>(a.pack.s_end[k], i0);
+    return t;
+}
+
+__device__ __forceinline__ bool tile_packs_state(const TileSpan& t) {
+    return t.c_beg < t.s_end[0] || t.c_beg < t.s_end[1] || t.c_beg < t.s_end[2];
+}
+
+// AdamW of one quad in registers.
+template <int kKind>
+__device__ __forceinline__ void update_quad(const StepScalars& s, u32x2 graw, f32x4& pv, f32x4& mv, f32x4& vv) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t word = graw[e >> 1];
+        const uint16_t gb = static_cast<uint16_t>((e & 1) ? (word >> 16) : (word & 0xFFFFu));
+        float p = pv[e], m = mv[e], v = vv[e];
+        adamw_update<kKind>(s, gb, p, m, v);
+        pv[e] = p;
+        mv[e] = m;
+        vv[e] = v;
+    }
+}
+
+// The quad at tile offset o into the ring, as far as the pack ranges reach
+// (they are multiples of 8 elements, so a quad lies inside one or outside).
+__device__ __forceinline__ void pack_quad(const PackPlan& pk, const TileSpan& t, int64_t i0, uint32_t o, u32x2 graw,
+                                          f32x4 pv, f32x4 mv, f32x4 vv) {
+    if (o < t.g_end) ring_st8(pk, pk.off_g + 2ull * static_cast<uint64_t>(i0) + 2u * o, graw);
+    if (o >= t.c_beg) {
+        const uint64_t rel = 4ull * static_cast<uint64_t>(i0 - pk.cb) + 4u * o;
+        if (o < t.s_end[0]) ring_st_f32x4(pk, pk.off_s[0] + rel, pv);
+        if (o < t.s_end[1]) ring_st_f32x4(pk, pk.off_s[1] + rel, mv);
+        if (o < t.s_end[2]) ring_st_f32x4(pk, pk.off_s[2] + rel, vv);
+    }
+}
+
+// The last n % 4 elements, one per thread.
+template <bool kHasW, int kKind>
+__device__ __forceinline__ void update_tail(const FusedArgs& a, const StepScalars& s, int skip) {
+    const PackPlan& pk = a.pack;
+    const int64_t i = a.n / 4 * 4 + threadIdx.x;
+    if (threadIdx.x >= 4 || i >= a.n) return;
+    const bool pack_g = !skip && i < pk.g_end;
+    const bool in_c = i >= pk.cb;
+    const uint16_t gb = a.g[i];
+    float p = a.p[i], m = a.m[i], v = a.v[i];
+    if (!skip) {
+        adamw_update<kKind>(s, gb, p, m, v);
+        a.p[i] = p;
+        a.m[i] = m;
+        a.v[i] = v;
+        if (kHasW) a.w[i] = f32_to_bf16_rne(p);
+    }
+    if (pack_g) ring_st_u16(pk, pk.off_g + 2ull * static_cast<uint64_t>(i), gb);
+    if (in_c) {
+        const uint64_t rel = 4ull * static_cast<uint64_t>(i - pk.cb);
+        if (i < pk.s_end[0]) ring_st_f32(pk, pk.off_s[0] + rel, p);
+        if (i < pk.s_end[1]) ring_st_f32(pk, pk.off_s[1] + rel, m);
+        if (i < pk.s_end[2]) ring_st_f32(pk, pk.off_s[2] + rel, v);
+    }
+}
+
 // A quad is 4 consecutive elements.  A block of kB threads owns a tile of
 // kB * kQ quads; thread t takes quads t, t + kB, ..., so every load and store
 // instruction of a wavefront covers 64 consecutive quads (1 KiB of fp32,
 // 512 B of bf16) and concurrently running blocks walk memory in order.  All
-// loads of a thread are issued before any arithmetic.  Chunk bounds are
-// multiples of 8, so a quad never straddles a part boundary.
+// loads of a thread are issued before any arithmetic.  Whether a tile is
+// whole, is skipped or packs anything is the same for the whole block, so the
+// tiles that only update -- nearly all outside a window -- run without a
+// predicate, on one base address per array.
+//
+// HBM bounds it, and how much of HBM's rate it gets depends on how many
+// wavefronts stream at once: with every wave slot filled (32 a compute unit)
+// the reads and writes of the five arrays disturb each other in the memory.
+// See launch_fused_q for the residency and what it measured.
 template <bool kHasW, int kQ, int kKind, bool kNT, int kB>
 __global__ __launch_bounds__(kB) void fused_kernel(FusedArgs a) {
+    constexpr uint32_t kTile = kB * kQ * 4;
     const gockpt_step_record* rec = a.rec;
     const int skip = rec->skip;
     StepScalars s;
@@ -415,87 +491,74 @@ __global__ __launch_bounds__(kB) void fused_kernel(FusedArgs a) {
     s.step_size = rec->step_size;
     s.sqrt_bc2 = rec->sqrt_bc2;
     s.inv_scale = rec->inv_scale;
-    const PackPlan& pk = a.pack;
 
-    const int64_t nquads = a.n / 4;
-    const int64_t q_base = static_cast<int64_t>(blockIdx.x) * (kB * kQ) + threadIdx.x;
-
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kTile;
+    const uint32_t live = tile_cut<kTile>(a.n & ~int64_t{3}, i0);  // the tile's whole quads end here
+    const uint16_t* gt = a.g + i0;
+    float* pt = a.p + i0;
+    float* mt = a.m + i0;
+    float* vt = a.v + i0;
+    uint16_t* wt = a.w + i0;
     u32x2 graw[kQ];
     f32x4 pv[kQ], mv[kQ], vv[kQ];
-    bool live[kQ], pk_g[kQ], pk_p[kQ], pk_m[kQ], pk_v[kQ];
+    const uint32_t o0 = threadIdx.x * 4u;
+    if (!skip && live == kTile) {
 #pragma unroll
-    for (int h = 0; h < kQ; ++h) {
-        const int64_t q = q_base + static_cast<int64_t>(h) * kB;
-        const int64_t i = q * 4;
-        live[h] = q < nquads;
-        pk_g[h] = live[h] && !skip && i < pk.g_end;  // a skipped step's gradients are never replayed
-        const bool in_c = live[h] && i >= pk.cb;
-        pk_p[h] = in_c && i < pk.s_end[0];
-        pk_m[h] = in_c && i < pk.s_end[1];
-        pk_v[h] = in_c && i < pk.s_end[2];
-        graw[h] = (u32x2){0u, 0u};
-        pv[h] = mv[h] = vv[h] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        if (live[h] && !skip) graw[h] = ld_stream<kNT>(reinterpret_cast<const u32x2*>(a.g + i));
-        if (live[h] && (!skip || pk_p[h] || pk_m[h] || pk_v[h])) {
-            pv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(a.p + i));
-            mv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(a.m + i));
-            vv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(a.v + i));
+        for (int h = 0; h < kQ; ++h) {
+            const uint32_t o = o0 + h * (kB * 4u);
+            graw[h] = ld_stream<kNT>(reinterpret_cast<const u32x2*>(gt + o));
+            pv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(pt + o));
+            mv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(mt + o));
+            vv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(vt + o));
         }
-    }
 #pragma unroll
-    for (int h = 0; h < kQ; ++h) {
-        if (!live[h]) continue;
-        const int64_t i = (q_base + static_cast<int64_t>(h) * kB) * 4;
-        if (!skip) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t word = graw[h][e >> 1];
-                const uint16_t gb = static_cast<uint16_t>((e & 1) ? (word >> 16) : (word & 0xFFFFu));
-                float p = pv[h][e], m = mv[h][e], v = vv[h][e];
-                adamw_update<kKind>(s, gb, p, m, v);
-                pv[h][e] = p;
-                mv[h][e] = m;
-                vv[h][e] = v;
-            }
-            st_stream<kNT>(reinterpret_cast<f32x4*>(a.p + i), pv[h]);
-            st_stream<kNT>(reinterpret_cast<f32x4*>(a.m + i), mv[h]);
-            st_stream<kNT>(reinterpret_cast<f32x4*>(a.v + i), vv[h]);
+        for (int h = 0; h < kQ; ++h) {
+            const uint32_t o = o0 + h * (kB * 4u);
+            update_quad<kKind>(s, graw[h], pv[h], mv[h], vv[h]);
+            st_stream<kNT>(reinterpret_cast<f32x4*>(pt + o), pv[h]);
+            st_stream<kNT>(reinterpret_cast<f32x4*>(mt + o), mv[h]);
+            st_stream<kNT>(reinterpret_cast<f32x4*>(vt + o), vv[h]);
             if (kHasW) {
                 const u32x2 wv = {pack2_bf16(pv[h][0], pv[h][1]), pack2_bf16(pv[h][2], pv[h][3])};
-                st_stream<kNT>(reinterpret_cast<u32x2*>(a.w + i), wv);
+                st_stream<kNT>(reinterpret_cast<u32x2*>(wt + o), wv);
             }
         }
-        if (pk_g[h]) ring_st8(pk, pk.off_g + 2ull * static_cast<uint64_t>(i), graw[h]);
-        const uint64_t rel = 4ull * static_cast<uint64_t>(i - pk.cb);
-        if (pk_p[h]) ring_st_f32x4(pk, pk.off_s[0] + rel, pv[h]);
-        if (pk_m[h]) ring_st_f32x4(pk, pk.off_s[1] + rel, mv[h]);
-        if (pk_v[h]) ring_st_f32x4(pk, pk.off_s[2] + rel, vv[h]);
-    }
-
-    // Ragged tail: the last n % 4 elements, one per thread of block 0.
-    if (blockIdx.x == 0 && threadIdx.x < 4) {
-        const int64_t i = nquads * 4 + threadIdx.x;
-        if (i < a.n) {
-            const bool pack_g = !skip && i < pk.g_end;
-            const bool in_c = i >= pk.cb;
-            const uint16_t gb = a.g[i];
-            float p = a.p[i], m = a.m[i], v = a.v[i];
+        if (a.pack.any) {
+            const TileSpan t = tile_span<kTile>(a, i0, 0);
+            if (t.g_end != 0u || tile_packs_state(t)) {
+#pragma unroll
+                for (int h = 0; h < kQ; ++h)
+                    pack_quad(a.pack, t, i0, o0 + h * (kB * 4u), graw[h], pv[h], mv[h], vv[h]);
+            }
+        }
+    } else if (live != 0u) {
+        // the last tile, or a skipped step (which only packs its part's
+        // unchanged state)
+        const TileSpan t = tile_span<kTile>(a, i0, skip);
+        const bool packs_state = tile_packs_state(t);
+#pragma unroll
+        for (int h = 0; h < kQ; ++h) {
+            const uint32_t o = o0 + h * (kB * 4u);
+            if (o >= live || (skip && !packs_state)) continue;
+            graw[h] = (u32x2){0u, 0u};
+            if (!skip) graw[h] = ld_stream<kNT>(reinterpret_cast<const u32x2*>(gt + o));
+            pv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(pt + o));
+            mv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(mt + o));
+            vv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(vt + o));
             if (!skip) {
-                adamw_update<kKind>(s, gb, p, m, v);
-                a.p[i] = p;
-                a.m[i] = m;
-                a.v[i] = v;
-                if (kHasW) a.w[i] = f32_to_bf16_rne(p);
+                update_quad<kKind>(s, graw[h], pv[h], mv[h], vv[h]);
+                st_stream<kNT>(reinterpret_cast<f32x4*>(pt + o), pv[h]);
+                st_stream<kNT>(reinterpret_cast<f32x4*>(mt + o), mv[h]);
+                st_stream<kNT>(reinterpret_cast<f32x4*>(vt + o), vv[h]);
+                if (kHasW) {
+                    const u32x2 wv = {pack2_bf16(pv[h][0], pv[h][1]), pack2_bf16(pv[h][2], pv[h][3])};
+                    st_stream<kNT>(reinterpret_cast<u32x2*>(wt + o), wv);
+                }
             }
-            if (pack_g) ring_st_u16(pk, pk.off_g + 2ull * static_cast<uint64_t>(i), gb);
-            if (in_c) {
-                const uint64_t rel = 4ull * static_cast<uint64_t>(i - pk.cb);
-                if (i < pk.s_end[0]) ring_st_f32(pk, pk.off_s[0] + rel, p);
-                if (i < pk.s_end[1]) ring_st_f32(pk, pk.off_s[1] + rel, m);
-                if (i < pk.s_end[2]) ring_st_f32(pk, pk.off_s[2] + rel, v);
-            }
+            pack_quad(a.pack, t, i0, o, graw[h], pv[h], mv[h], vv[h]);
         }
     }
+    if (blockIdx.x == 0) update_tail<kHasW, kKind>(a, s, skip);
 }
 
 // ---------------------------------------------------------------------------
@@ -592,23 +655,37 @@ static int launch_fused_q(const FusedArgs& a, hipStream_t s) {
     if (tiles < 1) tiles = 1;
     if (tiles > static_cast<int64_t>(0xFFFFFFFFu / kB)) return static_cast<int>(hipErrorInvalidValue);
     const unsigned grid = static_cast<unsigned>(tiles);
+    // Residency.  A block asks for LDS it never touches so that 12 of them,
+    // not 32, fit a compute unit: enough loads in flight for HBM's rate, and
+    // fewer streams in its way.  Measured on packed arrays (us a step,
+    // prepass included; 256-thread blocks without a limit | this block
+    // without one | 16 | 13 | 12 | 11 | 10 | 8 a compute unit):
+    //   1.63e9 elements   8454 | 7984 | 7710 | 7626 | 7710 | 7695 | 7862 | 8018
+    //   1.24e8 elements    662 |  628 |  609 |  591 |  588 |  612 |  597 |  625
+    //   1.68e7 elements   85.7 | 86.0 | 82.6 | 80.8 | 80.7 | 81.3 | 82.1 | 86.1
+    // Two or four quads a lane were no better at any of them.
+    const unsigned lds = kB == kFusedBlock && kQ == 1 ? kFusedLds : 0u;
     if (a.w != nullptr)
-        hipLaunchKernelGGL((fused_kernel<true, kQ, kKind, kNT, kB>), dim3(grid), dim3(kB), 0, s, a);
+        hipLaunchKernelGGL((fused_kernel<true, kQ, kKind, kNT, kB>), dim3(grid), dim3(kB), lds, s, a);
     else
-        hipLaunchKernelGGL((fused_kernel<false, kQ, kKind, kNT, kB>), dim3(grid), dim3(kB), 0, s, a);
+        hipLaunchKernelGGL((fused_kernel<false, kQ, kKind, kNT, kB>), dim3(grid), dim3(kB), lds, s, a);
     return static_cast<int>(hipGetLastError());
 }
 
-// Blocks of 1024 threads (16 wavefronts) only with one quad per lane, the
-// measured best; every other shape uses kBlock.
+// Blocks of 1024 threads (16 wavefronts) only with one quad per lane.
 template <int kKind, bool kNT>
 static int launch_fused_nt(const FusedArgs& a, hipStream_t s) {
     switch (a.quads_per_thread) {
-        case 4: return launch_fused_q<4, kKind, kNT, kBlock>(a, s);
-        case 2: return launch_fused_q<2, kKind, kNT, kBlock>(a, s);
+        case 4: return launch_fused_q<4, kKind, kNT, kFusedBlock>(a, s);
+        case 2: return launch_fused_q<2, kKind, kNT, kFusedBlock>(a, s);
         default:
-            return a.block == kFusedWideBlock ? launch_fused_q<1, kKind, kNT, kFusedWideBlock>(a, s)
-                                              : launch_fused_q<1, kKind, kNT, kBlock>(a, s);
+            if (a.block == kFusedWideBlock) return launch_fused_q<1, kKind, kNT, kFusedWideBlock>(a, s);
+            // up to two rounds of all wave slots (4.2e6 elements) latency
+            // bounds the launch: four times fewer blocks to start, and no
+            // residency limit (1.05e6 elements: 8.8 us a step with 256
+            // threads a block, 10.7 with 64; 8.4e6: 44.2 against 40.7)
+            return a.n <= 2 * kWaveSlots * int64_t{256} ? launch_fused_q<1, kKind, kNT, kBlock>(a, s)
+                                                        : launch_fused_q<1, kKind, kNT, kFusedBlock>(a, s);
     }
 }
 

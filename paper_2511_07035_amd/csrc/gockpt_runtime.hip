@@ -204,7 +204,7 @@ struct gockpt_ctx {
     hipStream_t cs = nullptr, xs = nullptr;
     uint8_t* ws = nullptr;
     int pre_blocks = 1;
-    Knobs knobs{1, 1, 1, 1, kBlock};
+    Knobs knobs{1, 1, 1, 1, kFusedBlock};
     size_t copy_bytes = GOCKPT_DEFAULT_COPY_BYTES;
     std::string err;
 
@@ -713,11 +713,10 @@ int create_ctx(const gockpt_config* cfg, uint8_t* ws, bool with_ctrl, gockpt_ctx
     c->ws = ws;
     c->pre_blocks = prepass_blocks_for(cfg->n);
     c->knobs = default_knobs();
-    // the fused kernel's block: kBlock unless asked for the 16-wavefront one
-    // (a few tenths of a percent faster on a GPU running nothing else, but a
-    // block that size cannot start on a compute unit another kernel partly
-    // holds, so it slows down badly beside concurrent kernels)
-    if (c->knobs.fused_block != kFusedWideBlock) c->knobs.fused_block = kBlock;
+    // the fused kernel's block: one wavefront unless asked for the
+    // 16-wavefront one (which cannot start on a compute unit another kernel
+    // partly holds, so it slows down badly beside concurrent kernels)
+    if (c->knobs.fused_block != kFusedWideBlock) c->knobs.fused_block = kFusedBlock;
     if (const char* f = getenv("GOCKPT_TEST_FAIL_COPY")) c->fail_copy_at = atoll(f);
     auto env_on = [](const char* name) {
         const char* v = getenv(name);
@@ -1368,6 +1367,7 @@ int gockpt_step(gockpt_ctx* c, float lr) {
         pk.g_end = ring_end[0];
         pk.cb = b0;
         for (int k = 0; k < 3; ++k) pk.s_end[k] = ring_end[k + 1];
+        pk.any = lpos != head0 ? 1 : 0;
         if (R) {
             pk.off_g = seg_lstart[0] % R;
             for (int k = 0; k < 3; ++k) pk.off_s[k] = seg_lstart[k + 1] % R;
