@@ -38,16 +38,45 @@ struct alignas(16) Partial {
 };
 static_assert(sizeof(Partial) == 16, "Partial");
 
+// One-launch steps (step_kernel): the tag of the next one's partials, and how
+// many blocks of the running one have read the state (each in one of
+// kStepArriveLanes counters, a line apart, and each full counter in `arrived`).
+struct alignas(64) StepSync {
+    uint32_t epoch;
+    uint32_t arrived;
+    uint32_t pad[14];
+};
+static_assert(sizeof(StepSync) == 64, "StepSync");
+struct alignas(256) StepArrive {
+    uint32_t count;
+};
+constexpr int kStepArriveLanes = 16;
+constexpr int kStepMaxTiles = 256;  // a thread of a block reads one partial
+static_assert(kStepMaxTiles == kBlock, "one partial per thread");
+constexpr int64_t kStepMaxElems = int64_t{kStepMaxTiles} * 512 * 2 * 4 + 3;  // two quads a lane, and the tail
+constexpr int kStepHelpSpins = 32;  // polls (about 1 us each) before a block computes the partials it misses
+
 static_assert(sizeof(gockpt_step_record) == 64, "record size");
 
 // Workspace layout: [DevScaler | pad to 256][records: (MAX_K+1) x 64]
 // [prepass partials][bucket-scan partials: two banks, alternating by step,
 // so the scans of the next step never overwrite what this step's finalize
 // still has to read]
+// The one-launch step keeps its sync words in the first pad and its slots in
+// the second half of the prepass partials: a space small enough for it has
+// at most kStepMaxElems / (kVec * kBlock) prepass blocks.
 constexpr size_t kWsScalerOff = 0;
+constexpr size_t kWsSyncOff = 64;
 constexpr size_t kWsRecordsOff = 256;
 constexpr size_t kWsPartialsOff = kWsRecordsOff + (GOCKPT_MAX_K + 1) * sizeof(gockpt_step_record);
 constexpr size_t kWsScanOff = kWsPartialsOff + kPrepassMaxBlocks * sizeof(Partial);
+// 256-byte aligned, as the workspace is
+constexpr size_t kWsSlotsOff = (kWsPartialsOff + kPrepassMaxBlocks / 2 * sizeof(Partial) + 255) / 256 * 256;
+constexpr size_t kWsArriveOff = kWsSlotsOff + kStepMaxTiles * sizeof(uint64_t);
+constexpr size_t kWsStepEnd = kWsArriveOff + kStepArriveLanes * sizeof(StepArrive);
+static_assert(kWsSyncOff + sizeof(StepSync) <= kWsRecordsOff, "sync words");
+static_assert(kWsArriveOff % 256 == 0 && kWsStepEnd <= kWsScanOff, "slots and counters");
+static_assert(kStepMaxElems / (kVec * kBlock) + 1 <= kPrepassMaxBlocks / 2, "slots beside the partials");
 constexpr size_t kWsBytes = kWsScanOff + 2 * kScanSlots * sizeof(Partial);
 
 // Page-locked, host-coherent control page of a context (4 KiB).  The device
@@ -116,6 +145,7 @@ struct Knobs {
     int prepass_nt;   // nontemporal gradient loads in the prepass
     int fused_nt;     // nontemporal loads and stores of the state in the fused kernel
     int fused_block;  // fused kernel threads per block: kFusedBlock (default) or kFusedWideBlock
+    bool defaults;    // none of the above asked for otherwise
 };
 
 // What the finalize of one step needs besides the partials.
@@ -145,6 +175,9 @@ int launch_scan(const uint16_t* g, int64_t begin, int64_t end, void* parts, int 
                 void* stream);
 int scan_blocks_for(int64_t count, int max_blocks);
 int launch_fused(const FusedArgs& a, void* stream);
+// The whole step in one launch: 1 <= n <= kStepMaxElems; joint: it tests the
+// gradients or sums their squares.
+int launch_step(const FusedArgs& a, const FinalizeArgs& fin, bool joint, void* workspace, void* stream);
 int prepass_blocks_for(int64_t n);
 Knobs default_knobs();
 

@@ -144,43 +144,23 @@ __device__ __forceinline__ uint32_t word_nonfinite(uint32_t w) {
 }
 
 // ---------------------------------------------------------------------------
-// Finalize: skip decision, loss scaler, step count, scalars, record.  Run by
-// one whole block of kBlock threads over the partials of the step.
+// End of a step, by one thread: skip decision, loss scaler, step count,
+// scalars, record.  `in` is the state before the step; acc and bad are the
+// step's sum of squares and inf/NaN flag.
 // ---------------------------------------------------------------------------
-__device__ void finalize_block(uint8_t* __restrict__ ws, const Partial* __restrict__ parts, int nparts,
-                               const FinalizeArgs& fa) {
-    // Thread t sums partials t, t + kBlock, ... in that order; the loads of
-    // eight of them are issued before any is added, so one block does not
-    // wait out eight memory latencies in a row.
-    double acc = 0.0;
-    uint32_t bad = 0u;
-    constexpr int kBatch = 8;
-    for (int b0 = 0; b0 < nparts; b0 += kBlock * kBatch) {
-        double v[kBatch];
-        int32_t f[kBatch];
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            const int b = b0 + k * kBlock + static_cast<int>(threadIdx.x);
-            v[k] = b < nparts ? parts[b].sumsq : 0.0;
-            f[k] = b < nparts ? parts[b].nonfinite : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            acc += v[k];
-            bad |= static_cast<uint32_t>(f[k]);
-        }
-    }
-    block_reduce<kBlock>(acc, bad);
-    if (threadIdx.x != 0) return;
-    // a caller-side overflow test replaces the scan (NaN counts as set)
-    if (fa.found_inf != nullptr) bad = (*fa.found_inf != 0.0f) ? 1u : 0u;
+struct StepState {
+    int64_t t, tracker;
+    float scale;
+};
 
+__device__ void finish_step(uint8_t* __restrict__ ws, const FinalizeArgs& fa, StepState in, double acc,
+                            uint32_t bad) {
     const ScalerCfg& sc = fa.sc;
     DevScaler* st = reinterpret_cast<DevScaler*>(ws + kWsScalerOff);
     gockpt_step_record* rec = reinterpret_cast<gockpt_step_record*>(ws + kWsRecordsOff) + fa.slot;
-    const float scale_used = st->scale;
-    int64_t t = st->t;
-    int64_t tracker = st->tracker;
+    const float scale_used = in.scale;
+    int64_t t = in.t;
+    int64_t tracker = in.tracker;
     float scale = scale_used;
     const int skip = (sc.check_overflow != 0 && bad != 0u) ? 1 : 0;
     if (skip) {
@@ -224,6 +204,42 @@ __device__ void finalize_block(uint8_t* __restrict__ ws, const Partial* __restri
     // the host reads the decision from its own memory once the step's
     // finalize has completed (vector store, system scope)
     if (fa.skip_out != nullptr) __hip_atomic_store(fa.skip_out, skip, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// ---------------------------------------------------------------------------
+// Finalize: one whole block of kBlock threads reduces the partials of the
+// step and ends it.
+// ---------------------------------------------------------------------------
+__device__ void finalize_block(uint8_t* __restrict__ ws, const Partial* __restrict__ parts, int nparts,
+                               const FinalizeArgs& fa) {
+    // Thread t sums partials t, t + kBlock, ... in that order; the loads of
+    // eight of them are issued before any is added, so one block does not
+    // wait out eight memory latencies in a row.
+    double acc = 0.0;
+    uint32_t bad = 0u;
+    constexpr int kBatch = 8;
+    for (int b0 = 0; b0 < nparts; b0 += kBlock * kBatch) {
+        double v[kBatch];
+        int32_t f[kBatch];
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            const int b = b0 + k * kBlock + static_cast<int>(threadIdx.x);
+            v[k] = b < nparts ? parts[b].sumsq : 0.0;
+            f[k] = b < nparts ? parts[b].nonfinite : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kBatch; ++k) {
+            acc += v[k];
+            bad |= static_cast<uint32_t>(f[k]);
+        }
+    }
+    block_reduce<kBlock>(acc, bad);
+    if (threadIdx.x != 0) return;
+    // a caller-side overflow test replaces the scan (NaN counts as set)
+    if (fa.found_inf != nullptr) bad = (*fa.found_inf != 0.0f) ? 1u : 0u;
+
+    const DevScaler* st = reinterpret_cast<const DevScaler*>(ws + kWsScalerOff);
+    finish_step(ws, fa, StepState{st->t, st->tracker, st->scale}, acc, bad);
 }
 
 // One 8-element group of gradients (16 B), nontemporal or cached.
@@ -562,6 +578,258 @@ __global__ __launch_bounds__(kB) void fused_kernel(FusedArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// A whole step in one launch, for small spaces (at most kStepMaxElems).
+//
+// Prepass, finalize and update as launches of their own cost about 3.7 us
+// each however little they do, and the gradients are read twice.  Here each
+// block keeps its tile in registers from the inf/NaN test to the update, and
+// the blocks exchange their partial sums through memory in between, so every
+// byte is read once.  Latency bounds it: the launch, one round of loads, the
+// exchange (about 1.5 us) and one round of stores.  Steps one after the other
+// on one stream, three launches against one: 11.0 us and 7.7 for 65560
+// elements, 11.4 and 9.0 for 524288, 11.1 and 10.2 for 1048579; without
+// anything to exchange 6.1, 6.8 and 8.3.
+//
+// The exchange needs no block to be running beside another one.  A block that
+// has waited kStepHelpSpins polls for a partial computes the missing ones
+// itself: a partial depends on the gradients alone, which nothing writes
+// during the kernel, so whoever computes it publishes the same bits.  Every
+// running block can therefore finish on its own, and a block that starts late
+// finds all partials there and updates its own tile.  The loss-scaler state
+// is read by every block and moved on by the last one to have read it.
+//
+// A partial is one 64-bit word, the sum (a double without its sign and its 11
+// last bits: 2^-41 relative, against 2^-24 for the prepass's fp32 squares)
+// and a tag of 12 bits, the step's epoch, which the last block moves on too.
+// A reader thus needs no order between the partial and a flag: no fence,
+// which on this chip would write back an XCD's L2.  Every step writes every
+// slot, so a slot that does not hold this epoch's tag holds the last one's.
+// A sum of squares in fp64 is finite exactly when every gradient is, so the
+// inf/NaN flag needs no bits of its own.
+// ---------------------------------------------------------------------------
+struct StepIn {  // what a block reads of the workspace
+    StepState st;
+    uint32_t epoch;
+};
+
+template <class T>
+__device__ __forceinline__ T ld_agent(const T* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sum over the block, the same bits in every thread.  `lds` is not reused
+// before the next barrier but one.
+template <int kB>
+__device__ __forceinline__ double block_sum(double x, double* lds) {
+    x = wave_sum(x);
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = x;
+    __syncthreads();
+    double t = 0.0;
+#pragma unroll
+    for (int w = 0; w < kB / 64; ++w) t += lds[w];
+    return t;
+}
+
+template <int kKind>
+__device__ __forceinline__ double quad_sumsq(u32x2 g) {
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t word = g[e >> 1];
+        const double x = static_cast<double>(
+            norm_value<kKind>(static_cast<uint16_t>((e & 1) ? (word >> 16) : (word & 0xFFFFu))));
+        acc += x * x;
+    }
+    return acc;
+}
+
+// Sum of squares of the scaled gradients of tile b (the last n % 4 belong to
+// tile 0), given its quads or loading them.
+template <int kB, int kQ, int kKind>
+__device__ __forceinline__ double tile_sumsq(const FusedArgs& a, int b, const u32x2* graw, double* lds) {
+    constexpr uint32_t kTile = kB * kQ * 4;
+    const int64_t i0 = static_cast<int64_t>(b) * kTile;
+    const uint32_t live = tile_cut<kTile>(a.n & ~int64_t{3}, i0);
+    double acc = 0.0;
+#pragma unroll
+    for (int h = 0; h < kQ; ++h) {
+        const uint32_t o = threadIdx.x * 4u + h * (kB * 4u);
+        u32x2 g = {0u, 0u};
+        if (graw != nullptr)
+            g = graw[h];
+        else if (o < live)
+            g = *reinterpret_cast<const u32x2*>(a.g + i0 + o);
+        acc += quad_sumsq<kKind>(g);
+    }
+    if (b == 0 && threadIdx.x < 4) {
+        const int64_t i = (a.n & ~int64_t{3}) + threadIdx.x;
+        if (i < a.n) {
+            const double x = static_cast<double>(norm_value<kKind>(a.g[i]));
+            acc += x * x;
+        }
+    }
+    return block_sum<kB>(acc, lds);
+}
+
+constexpr uint64_t kSlotTagMask = 0xFFF;
+
+__device__ __forceinline__ void publish(uint64_t* slot, uint32_t epoch, double x) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, x) << 1;
+    __hip_atomic_store(slot, (u & ~kSlotTagMask) | (epoch & kSlotTagMask), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double slot_value(uint64_t w) {
+    return __builtin_bit_cast(double, (w & ~kSlotTagMask) >> 1);
+}
+
+// Counts this block in; true for the last of `tiles` blocks.  Two levels: one
+// counter for all of them took 12 ns a block, 3 us for 256.
+__device__ __forceinline__ bool arrive_last(StepSync* sync, StepArrive* lanes, int tiles) {
+    const int lane = blockIdx.x % kStepArriveLanes;
+    const uint32_t here = (tiles - lane + kStepArriveLanes - 1) / kStepArriveLanes;  // blocks of this lane
+    const uint32_t used = tiles < kStepArriveLanes ? tiles : kStepArriveLanes;
+    if (__hip_atomic_fetch_add(&lanes[lane].count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u != here)
+        return false;
+    return __hip_atomic_fetch_add(&sync->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == used;
+}
+
+// kJoint: the step needs the sum over all gradients (overflow test or norm);
+// without it nothing is exchanged.
+template <bool kHasW, int kB, int kQ, int kKind, bool kJoint>
+__global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, uint8_t* __restrict__ ws) {
+    constexpr uint32_t kTile = kB * kQ * 4;
+    __shared__ StepScalars s_sc;
+    __shared__ uint32_t s_epoch, s_found;
+    __shared__ double s_sum[2][kB / 64];
+    __shared__ uint8_t s_missing[kStepMaxTiles];
+    const int tid = threadIdx.x;
+    const int tiles = gridDim.x;
+    StepSync* sync = reinterpret_cast<StepSync*>(ws + kWsSyncOff);
+    uint64_t* slots = reinterpret_cast<uint64_t*>(ws + kWsSlotsOff);
+    StepArrive* lanes = reinterpret_cast<StepArrive*>(ws + kWsArriveOff);
+
+    StepIn in{};
+    float found = 0.0f;
+    if (tid == 0) {
+        const DevScaler* st = reinterpret_cast<const DevScaler*>(ws + kWsScalerOff);
+        in.st = StepState{st->t, st->tracker, st->scale};
+        in.epoch = sync->epoch;
+        if (fa.found_inf != nullptr) found = *fa.found_inf;
+    }
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * kTile;
+    const uint32_t live = tile_cut<kTile>(a.n & ~int64_t{3}, i0);
+    const uint32_t o0 = tid * 4u;
+    u32x2 graw[kQ];
+    f32x4 pv[kQ], mv[kQ], vv[kQ];
+#pragma unroll
+    for (int h = 0; h < kQ; ++h) {
+        const uint32_t o = o0 + h * (kB * 4u);
+        graw[h] = (u32x2){0u, 0u};
+        pv[h] = mv[h] = vv[h] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (o < live) {
+            graw[h] = *reinterpret_cast<const u32x2*>(a.g + i0 + o);
+            pv[h] = *reinterpret_cast<const f32x4*>(a.p + i0 + o);
+            mv[h] = *reinterpret_cast<const f32x4*>(a.m + i0 + o);
+            vv[h] = *reinterpret_cast<const f32x4*>(a.v + i0 + o);
+        }
+    }
+    bool last = false;
+    if (tid == 0) {
+        // the state is in registers before the arrival is counted: the last
+        // block to arrive overwrites it
+        asm volatile("" : "+v"(in.st.t), "+v"(in.st.tracker), "+v"(in.st.scale), "+v"(in.epoch) : : "memory");
+        s_epoch = in.epoch;
+        s_found = found != 0.0f ? 1u : 0u;  // a NaN flag counts as set
+        s_sc = step_scalars(fa.hp, fa.lr, in.st.t + 1, in.st.scale);
+    }
+
+    double mine = 0.0;
+    if constexpr (kJoint)
+        mine = tile_sumsq<kB, kQ, kKind>(a, blockIdx.x, graw, s_sum[0]);
+    else
+        __syncthreads();
+    const uint32_t epoch = s_epoch;
+    if (tid == 0) {
+        if (kJoint) publish(slots + blockIdx.x, epoch, mine);
+        last = arrive_last(sync, lanes, tiles);
+    }
+
+    // the update itself while the partials travel, in registers: only its
+    // stores wait for the decision
+    const StepScalars s = s_sc;
+    u32x2 wv[kQ];
+#pragma unroll
+    for (int h = 0; h < kQ; ++h) {
+        update_quad<kKind>(s, graw[h], pv[h], mv[h], vv[h]);
+        wv[h] = (u32x2){pack2_bf16(pv[h][0], pv[h][1]), pack2_bf16(pv[h][2], pv[h][3])};
+    }
+
+    double acc = 0.0;
+    if constexpr (kJoint) {
+        uint64_t word = 0;
+        bool have = tid >= tiles;
+        for (int spins = 0;; ++spins) {
+            if (!have) {
+                word = ld_agent(slots + tid);
+                have = (word & kSlotTagMask) == (epoch & kSlotTagMask);
+            }
+            if (__syncthreads_and(have)) break;
+            if (spins % kStepHelpSpins == kStepHelpSpins - 1) {
+                if (tid < kStepMaxTiles) s_missing[tid] = have ? 0 : 1;
+                __syncthreads();
+                for (int b = 0; b < tiles; ++b) {
+                    if (!s_missing[b]) continue;
+                    const double x = tile_sumsq<kB, kQ, kKind>(a, b, nullptr, s_sum[0]);
+                    if (tid == 0) publish(slots + b, epoch, x);
+                    __syncthreads();
+                }
+            }
+        }
+        acc = block_sum<kB>(tid < tiles ? slot_value(word) : 0.0, s_sum[1]);
+    }
+    uint32_t bad = (__builtin_bit_cast(uint64_t, acc) & 0x7FF0000000000000ull) == 0x7FF0000000000000ull ? 1u : 0u;
+    if (fa.found_inf != nullptr) bad = s_found;
+    const int skip = (fa.sc.check_overflow != 0 && bad != 0u) ? 1 : 0;
+
+    if (!skip) {
+#pragma unroll
+        for (int h = 0; h < kQ; ++h) {
+            const uint32_t o = o0 + h * (kB * 4u);
+            if (o >= live) continue;
+            *reinterpret_cast<f32x4*>(a.p + i0 + o) = pv[h];
+            *reinterpret_cast<f32x4*>(a.m + i0 + o) = mv[h];
+            *reinterpret_cast<f32x4*>(a.v + i0 + o) = vv[h];
+            if (kHasW) *reinterpret_cast<u32x2*>(a.w + i0 + o) = wv[h];
+        }
+    }
+    if (a.pack.any) {
+        const TileSpan t = tile_span<kTile>(a, i0, skip);
+        const bool packs_state = tile_packs_state(t);
+        if (t.g_end != 0u || packs_state) {
+#pragma unroll
+            for (int h = 0; h < kQ; ++h) {
+                const uint32_t o = o0 + h * (kB * 4u);
+                if (o >= live) continue;
+                if (skip) {  // the registers hold an update that is not applied
+                    pv[h] = *reinterpret_cast<const f32x4*>(a.p + i0 + o);
+                    mv[h] = *reinterpret_cast<const f32x4*>(a.m + i0 + o);
+                    vv[h] = *reinterpret_cast<const f32x4*>(a.v + i0 + o);
+                }
+                pack_quad(a.pack, t, i0, o, graw[h], pv[h], mv[h], vv[h]);
+            }
+        }
+    }
+    if (blockIdx.x == 0) update_tail<kHasW, kKind>(a, s, skip);
+
+    if (last) {
+        for (int k = 0; k < kStepArriveLanes; ++k) lanes[k].count = 0u;
+        sync->arrived = 0u;
+        sync->epoch = in.epoch + 1u;
+        finish_step(ws, fa, in.st, acc, bad);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
 static int env_int(const char* name, int dflt) {
@@ -611,6 +879,8 @@ Knobs default_knobs() {
     k.prepass_nt = env_int("GOCKPT_PREPASS_NT", 1);
     k.fused_nt = env_int("GOCKPT_FUSED_NT", 1);
     k.fused_block = env_int("GOCKPT_FUSED_BLOCK", 0);
+    k.defaults = k.quads_per_thread == 1 && k.ring_nt == 1 && k.prepass_nt == 1 && k.fused_nt == 1 &&
+                 k.fused_block != kFusedWideBlock;
     return k;
 }
 
@@ -687,6 +957,39 @@ static int launch_fused_nt(const FusedArgs& a, hipStream_t s) {
             return a.n <= 2 * kWaveSlots * int64_t{256} ? launch_fused_q<1, kKind, kNT, kBlock>(a, s)
                                                         : launch_fused_q<1, kKind, kNT, kFusedBlock>(a, s);
     }
+}
+
+template <int kB, int kQ, int kKind, bool kJoint>
+static int launch_step_q(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, hipStream_t s) {
+    const int64_t per_block = static_cast<int64_t>(kB) * kQ * 4;
+    int64_t tiles = (a.n / 4 * 4 + per_block - 1) / per_block;
+    if (tiles < 1) tiles = 1;
+    if (tiles > kStepMaxTiles) return static_cast<int>(hipErrorInvalidValue);
+    const unsigned grid = static_cast<unsigned>(tiles);
+    if (a.w != nullptr)
+        hipLaunchKernelGGL((step_kernel<true, kB, kQ, kKind, kJoint>), dim3(grid), dim3(kB), 0, s, a, fa, ws);
+    else
+        hipLaunchKernelGGL((step_kernel<false, kB, kQ, kKind, kJoint>), dim3(grid), dim3(kB), 0, s, a, fa, ws);
+    return static_cast<int>(hipGetLastError());
+}
+
+template <int kKind, bool kJoint>
+static int launch_step_n(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, hipStream_t s) {
+    const int64_t quads = a.n / 4, row = static_cast<int64_t>(kStepMaxTiles) * kBlock;
+    // at most 256 tiles, so that a thread polls one partial; beyond 256 rows of
+    // one quad per 256 threads, blocks of 512 (1.05e6 elements: 10.2 us with
+    // two quads a lane, 11.2 with 256 threads and four)
+    if (quads <= row) return launch_step_q<kBlock, 1, kKind, kJoint>(a, fa, ws, s);
+    if (quads <= 2 * row) return launch_step_q<2 * kBlock, 1, kKind, kJoint>(a, fa, ws, s);
+    return launch_step_q<2 * kBlock, 2, kKind, kJoint>(a, fa, ws, s);
+}
+
+int launch_step(const FusedArgs& a, const FinalizeArgs& fin, bool joint, void* workspace, void* stream) {
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    uint8_t* ws = static_cast<uint8_t*>(workspace);
+    if (a.grad_kind == kGradFP16)
+        return joint ? launch_step_n<kGradFP16, true>(a, fin, ws, s) : launch_step_n<kGradFP16, false>(a, fin, ws, s);
+    return joint ? launch_step_n<kGradBF16, true>(a, fin, ws, s) : launch_step_n<kGradBF16, false>(a, fin, ws, s);
 }
 
 template <int kKind>

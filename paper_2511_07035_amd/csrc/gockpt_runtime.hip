@@ -204,7 +204,7 @@ struct gockpt_ctx {
     hipStream_t cs = nullptr, xs = nullptr;
     uint8_t* ws = nullptr;
     int pre_blocks = 1;
-    Knobs knobs{1, 1, 1, 1, kFusedBlock};
+    Knobs knobs{1, 1, 1, 1, kFusedBlock, true};
     size_t copy_bytes = GOCKPT_DEFAULT_COPY_BYTES;
     std::string err;
 
@@ -750,11 +750,19 @@ int create_ctx(const gockpt_config* cfg, uint8_t* ws, bool with_ctrl, gockpt_ctx
         }
     }
     if (he == hipSuccess) {
-        DevScaler init{};
-        init.t = cfg->init_step;
-        init.tracker = cfg->init_tracker;
-        init.scale = cfg->init_scale;
+        struct {
+            DevScaler sc;
+            StepSync sync;
+        } init{};
+        static_assert(offsetof(decltype(init), sync) == kWsSyncOff && kWsScalerOff == 0, "one upload");
+        init.sc.t = cfg->init_step;
+        init.sc.tracker = cfg->init_tracker;
+        init.sc.scale = cfg->init_scale;
+        init.sync.epoch = 1;
+        const std::vector<uint8_t> zero(kWsStepEnd - kWsSlotsOff, 0);
         he = hipMemcpyAsync(c->ws + kWsScalerOff, &init, sizeof init, hipMemcpyHostToDevice, c->cs);
+        if (he == hipSuccess)
+            he = hipMemcpyAsync(c->ws + kWsSlotsOff, zero.data(), zero.size(), hipMemcpyHostToDevice, c->cs);
         if (he == hipSuccess) he = hipStreamSynchronize(c->cs);
     }
     if (he != hipSuccess) {
@@ -1262,7 +1270,17 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     const bool scanned = !c->scan_ranges.empty();
     const bool prepass =
         !scanned && n > 0 && ((cfg.check_overflow != 0 && fin.found_inf == nullptr) || cfg.grad_norm_off == 0);
-    if (prepass) {
+    // A small space takes the whole step in one launch (step_kernel), queued
+    // where the update would be.  Up to kStepMaxElems, as far as its blocks
+    // hold their tiles in registers; there it is still the faster one (10.2 us
+    // against 11.1).
+    // Not with bucket scans (their partials are reduced by the finalize), nor
+    // where the finalize has to end before the update is launched: the
+    // HOST_WAIT plan reads its decision, and timing events stand around both.
+    // The launch-shape knobs belong to the separate kernels.
+    const bool one_launch = n > 0 && n <= kStepMaxElems && !scanned && !timed && c->knobs.defaults &&
+                            !(in_window && c->ring_plan == GOCKPT_RING_HOST_WAIT && R);
+    if (prepass && !one_launch) {
         e = static_cast<hipError_t>(
             launch_prepass(cfg.grad16, n, c->ws, c->pre_blocks, c->knobs.prepass_nt, cfg.grad_dtype, c->cs));
         if (e != hipSuccess) return c->hip_fail(e, "prepass launch");
@@ -1273,10 +1291,12 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     const uint8_t* parts = c->ws + (scanned ? kWsScanOff + static_cast<size_t>(c->scan_bank) * kScanSlots *
                                                                sizeof(Partial)
                                             : kWsPartialsOff);
-    fin.raw = scanned ? 1 : 0;
-    e = static_cast<hipError_t>(
-        launch_finalize(c->ws, parts, scanned ? c->scan_used : (prepass ? c->pre_blocks : 0), fin, c->cs));
-    if (e != hipSuccess) return c->hip_fail(e, "finalize launch");
+    fin.raw = scanned || one_launch ? 1 : 0;
+    if (!one_launch) {
+        e = static_cast<hipError_t>(
+            launch_finalize(c->ws, parts, scanned ? c->scan_used : (prepass ? c->pre_blocks : 0), fin, c->cs));
+        if (e != hipSuccess) return c->hip_fail(e, "finalize launch");
+    }
     if (scanned) {  // the next step's scans fill the other bank
         std::lock_guard<std::mutex> lk(c->mu);
         for (const auto& se : c->scan_events) c->event_pool.push_back(se.second);
@@ -1423,7 +1443,10 @@ int gockpt_step(gockpt_ctx* c, float lr) {
         }
     }
     if (timed && (e = hipEventRecord(tm.upd0, c->cs)) != hipSuccess) return c->hip_fail(e, "event record");
-    if (n > 0) {
+    if (one_launch) {
+        if ((e = static_cast<hipError_t>(launch_step(a, fin, prepass, c->ws, c->cs))) != hipSuccess)
+            return c->hip_fail(e, "step launch");
+    } else if (n > 0) {
         if ((e = static_cast<hipError_t>(launch_fused(a, c->cs))) != hipSuccess) return c->hip_fail(e, "fused launch");
     }
     if (timed && (e = hipEventRecord(tm.upd1, c->cs)) != hipSuccess) return c->hip_fail(e, "event record");

@@ -18,3 +18,82 @@ def test_update_shapes_same_bits(n):
     _, stats, _ = _run_window(n, 3, bounds, seed=n % 97, ring_bytes=12 << 20, copy_bytes=4 << 20, dynamic=True,
                               inf_steps=(3,), late_plan=2)
     assert stats.bytes_spilled > 0 and stats.bytes_ring > 0 and stats.skipped == 1
+
+
+ROW = 256 * 256 * 4  # elements of a one-launch step with one quad a lane
+
+
+@pytest.mark.parametrize("n", [1, 6, 1024, 1028, ROW, ROW + 1, 2 * ROW, 2 * ROW + 4, 4 * ROW + 3, 4 * ROW + 4])
+@pytest.mark.parametrize("grad_dtype", ["bf16", "fp16"])
+def test_one_launch_step_same_bits(n, grad_dtype):
+    """Small spaces take the whole step in one launch: at the sizes where its
+    tiling changes and the first size beyond it, with a skipped step, dynamic
+    scaling, a pack into a ring that wraps and spills, and the norm."""
+    K = 4 if n >= 64 else 1
+    bounds = [0] + [n * k // K // 8 * 8 for k in range(1, K)] + [n]
+    ring = max(256, n * 5 // 2 // 256 * 256)
+    _, stats, _ = _run_window(n, K, bounds, seed=n % 89, ring_bytes=ring, copy_bytes=1 << 20, dynamic=True,
+                              inf_steps=(3,) if K > 1 else (), late_plan=2, grad_dtype=grad_dtype)
+    assert stats.skipped == (1 if K > 1 else 0)
+
+
+@pytest.mark.parametrize("kw", [dict(check_overflow=False, grad_norm=False), dict(check_overflow=False),
+                                dict(grad_norm=False, found_inf=[0.0, 1.0, 0.0]), dict(found_inf=[0.0, 1.0, 0.0]),
+                                dict(grad_norm=False, with_weight=False)])
+def test_one_launch_step_options(kw):
+    """The step with and without something to exchange between its blocks."""
+    n = 300_005
+    _run_window(n, 3, [0, 100_000, 200_008, n], seed=61, ring_bytes=1 << 20, **kw)
+
+
+def test_one_launch_step_beside_a_full_device():
+    """The blocks of a one-launch step need not run together: with another
+    kernel on all but a few of the device's places, those that run compute the
+    partials of those that cannot start yet, and the step ends, with the
+    oracle's bits, long before the other kernel does.  Whether a block finds
+    one of the places left is the device's choice (its shader engines take
+    blocks in turn, and both streams may share a hardware queue), so the bits
+    are checked for every number of places, and that the step ran beside the
+    other kernel for those where it could."""
+    import time
+
+    import numpy as np
+    import torch
+
+    import bench
+    import oracle
+    import synth
+    from gpu_util import assert_bits_equal, load_state, to_device_grad16
+    from paper_2511_07035_amd import Session
+
+    n = ROW
+    places = 8 * torch.cuda.get_device_properties(0).multi_processor_count  # blocks of four wavefronts
+    cfg = oracle.AdamWConfig()
+    p0 = synth.master_cpu(n, 71)
+    ref = oracle.State(p0)
+    L = bench.bench_lib()
+    side = torch.cuda.Stream()
+    beside = []
+    with Session(n, ring_bytes=0) as sess:
+        load_state(sess, p0, w=ref.w)
+        for k, free_blocks in enumerate((64, 96, 192), 1):
+            g = synth.grads_cpu(n, 71, k)
+            to_device_grad16(sess, g)
+            torch.cuda.synchronize()
+            hog_end, step_end = torch.cuda.Event(), torch.cuda.Event()
+            assert L.gockpt_bench_hog(side.cuda_stream, 100.0, places - free_blocks) == 0
+            hog_end.record(side)
+            time.sleep(0.01)  # it holds its places before the step is queued
+            sess.step(cfg.lr)
+            step_end.record(sess.compute)
+            step_end.synchronize()
+            beside.append(not hog_end.query())
+            oracle.adamw_step(ref, g, cfg)
+            torch.cuda.synchronize()
+            p, m, v, w = sess.state_to_host()
+            assert_bits_equal(p, ref.p, "master")
+            assert_bits_equal(m, ref.m, "exp_avg")
+            assert_bits_equal(v, ref.v, "exp_avg_sq")
+            assert np.array_equal(w, ref.w)
+    if not any(beside):
+        pytest.skip("the device ran the step after the other kernel each time")
