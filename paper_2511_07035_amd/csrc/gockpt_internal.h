@@ -15,6 +15,15 @@ constexpr int kFusedWideBlock = 1024;   // the fused kernel's optional wide bloc
 constexpr int kWaveSlots = 256 * 32;     // wavefronts the device holds at once
 constexpr unsigned kFusedLds = 13312;   // LDS of a fused block under the residency limit: 12 blocks a compute unit
 constexpr int kVec = 8;                 // elements per thread per group
+// Loads a lane of the prepass and of a bucket scan keeps in flight beside the
+// current ones.  A scan beside the backward has one block a compute unit, so
+// memory latency bounds it: with 8 buckets of 15.6e6 elements 632 us a step
+// with one load, 617 with four, 618 with eight (350e6 elements: 1800, 1718,
+// 1721).  The prepass fills the device: one, two, four or eight loads are
+// within 1% from 8.4e6 elements on; below, two were 3% faster (2.1e6: 15.0,
+// 14.5, 15.0, 16.4 us a step).
+constexpr int kPrepassAhead = 2;
+constexpr int kScanAhead = 4;
 constexpr int kPrepassMaxBlocks = 2048; // partial sums slots
 constexpr int kFinalizeThreads = 256;
 constexpr int kScanSlots = 8192;        // partials of the bucket scans of one step

@@ -248,6 +248,30 @@ __device__ __forceinline__ u32x4 ld_group(const uint16_t* p) {
     return kNT ? __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p)) : ld_u32x4(p);
 }
 
+// Calls f(group) for this thread's groups gi, gi + stride, ... below ngroups
+// (a multiple of kAhead of them: zeros stand in beyond the end).  The next
+// kAhead loads are issued before the arithmetic of the current ones.
+template <bool kNT, int kAhead, class F>
+__device__ __forceinline__ void each_group(const uint16_t* g, int64_t gi, int64_t stride, int64_t ngroups, F&& f) {
+    u32x4 next[kAhead];
+    auto load = [&](int64_t first) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            next[u] = (u32x4){0u, 0u, 0u, 0u};
+            if (first + u * stride < ngroups) next[u] = ld_group<kNT>(g + (first + u * stride) * kVec);
+        }
+    };
+    load(gi);
+    for (; gi < ngroups; gi += kAhead * stride) {
+        u32x4 raw[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) raw[u] = next[u];
+        load(gi + kAhead * stride);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) f(raw[u]);
+    }
+}
+
 template <bool kNT, int kKind>
 __global__ __launch_bounds__(kBlock) void prepass_kernel(const uint16_t* __restrict__ g, int64_t n,
                                                          uint8_t* __restrict__ ws) {
@@ -258,14 +282,7 @@ __global__ __launch_bounds__(kBlock) void prepass_kernel(const uint16_t* __restr
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
     double acc = 0.0;
     uint32_t bad = 0u;
-    // the next group's load is issued before this group's arithmetic, so a
-    // wave keeps a load in flight while it computes
-    int64_t gi = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
-    u32x4 next = (u32x4){0u, 0u, 0u, 0u};
-    if (gi < ngroups) next = ld_group<kNT>(g + gi * kVec);
-    for (; gi < ngroups; gi += stride) {
-        const u32x4 raw = next;
-        if (gi + stride < ngroups) next = ld_group<kNT>(g + (gi + stride) * kVec);
+    each_group<kNT, kPrepassAhead>(g, static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x, stride, ngroups, [&](u32x4 raw) {
         float s = 0.0f;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -277,7 +294,7 @@ __global__ __launch_bounds__(kBlock) void prepass_kernel(const uint16_t* __restr
             s = s + b * b;
         }
         acc += static_cast<double>(s);
-    }
+    });
     if (blockIdx.x == 0) {
         const int64_t i = ngroups * kVec + threadIdx.x;
         if (threadIdx.x < kVec && i < n) {
@@ -312,12 +329,7 @@ __global__ __launch_bounds__(kBlock) void scan_kernel(const uint16_t* __restrict
     const uint16_t* base = g + begin;
     double acc = 0.0;
     uint32_t bad = 0u;
-    int64_t gi = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;  // next load in flight, as the prepass
-    u32x4 next = (u32x4){0u, 0u, 0u, 0u};
-    if (gi < ngroups) next = ld_group<kNT>(base + gi * kVec);
-    for (; gi < ngroups; gi += stride) {
-        const u32x4 raw = next;
-        if (gi + stride < ngroups) next = ld_group<kNT>(base + (gi + stride) * kVec);
+    each_group<kNT, kScanAhead>(base, static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x, stride, ngroups, [&](u32x4 raw) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             const uint32_t w = raw[k];
@@ -327,7 +339,7 @@ __global__ __launch_bounds__(kBlock) void scan_kernel(const uint16_t* __restrict
             acc += a * a;
             acc += b * b;
         }
-    }
+    });
     if (blockIdx.x == 0) {
         const int64_t i = begin + ngroups * kVec + threadIdx.x;
         if (threadIdx.x < kVec && i < end) {
