@@ -282,7 +282,8 @@ typedef struct {
                                  packs none of its gradients) */
     uint64_t bytes_spilled;   /* bytes copied straight from live buffers */
     uint64_t bytes_d2h;       /* all bytes copied to the host arena */
-    uint64_t n_copies;        /* hipMemcpyAsync calls */
+    uint64_t n_copies;        /* copies queued: hipMemcpyAsync calls, or one kernel
+                                 for all copies of a step of at most 1 MiB */
     double copy_ms;           /* sum over steps of copy-stream busy time */
     double prepass_ms;        /* sum over steps of the time before the update:
                                  prepass (or the wait for the bucket scans)

@@ -147,6 +147,26 @@ struct FusedArgs {
     PackPlan pack;
 };
 
+// The copies of one window step of at most kGatherMaxBytes, queued as one
+// kernel (gather_kernel) instead of one DMA transfer each.  The kernel was the
+// faster one at every size measured (to the drain of a 4-step window with
+// 2.4 MB a step 272 us against 453, 9.4 MB 742 against 881), but it runs on
+// compute units and its stores to the link hold up what runs beside it (a
+// matrix product by half while it lasts), so it gets at most 1 MiB: 18 us.
+//
+// The ranges: the record, four in the ring, one of which may wrap, and four of
+// the live buffers.
+constexpr uint64_t kGatherMaxBytes = 1 << 20;
+constexpr int kGatherSegs = 12;
+constexpr uint64_t kGatherBlocks = 16;  // blocks per range
+struct GatherArgs {
+    struct {
+        const uint8_t* src;  // device, 16-byte aligned
+        uint8_t* dst;        // device address of pinned host memory, 16-byte aligned
+        uint64_t bytes;
+    } seg[kGatherSegs];
+};
+
 // Launch-shape choices of a context (fixed at create).
 struct Knobs {
     int quads_per_thread;  // fused kernel: quads of 4 elements per thread
@@ -176,6 +196,8 @@ int launch_prepass(const uint16_t* g, int64_t n, void* workspace, int nblocks, i
 // parts: the partials to reduce (nparts of them, in order); raw: they hold
 // squares of the scaled gradients (bucket scans), which the finalize unscales.
 int launch_finalize(void* workspace, const void* parts, int nparts, const FinalizeArgs& fin, void* stream);
+// Copies nseg ranges to pinned host memory in one launch.
+int launch_gather(const GatherArgs& a, int nseg, void* stream);
 // One wavefront on `stream` that waits until *released >= target (host-
 // coherent memory the host advances), at most max_ticks of the 100 MHz
 // constant clock; on giving up it sets *timed_out.

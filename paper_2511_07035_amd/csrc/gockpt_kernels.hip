@@ -389,6 +389,24 @@ __global__ __launch_bounds__(64) void gate_kernel(const uint64_t* released, uint
 }
 
 // ---------------------------------------------------------------------------
+// The copies of a small window step to pinned host memory, one launch instead
+// of a DMA transfer per range, blockIdx.y per range.  The link bounds the
+// bytes (57 GB/s), the calls a small step: a window of 4 steps over 65560
+// elements took 378 us to its drain with 19 transfers and 193 with 4 launches,
+// over 262144 elements 378 and 205.  See kGatherMaxBytes for where it stops.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void gather_kernel(GatherArgs a) {
+    const uint8_t* src = a.seg[blockIdx.y].src;
+    uint8_t* dst = a.seg[blockIdx.y].dst;
+    const uint64_t bytes = a.seg[blockIdx.y].bytes;
+    const uint64_t units = bytes / 16;
+    for (uint64_t u = static_cast<uint64_t>(blockIdx.x) * kBlock + threadIdx.x; u < units;
+         u += static_cast<uint64_t>(gridDim.x) * kBlock)
+        __builtin_nontemporal_store(ld_u32x4(src + u * 16), reinterpret_cast<u32x4*>(dst + u * 16));
+    if (blockIdx.x == 0 && threadIdx.x < bytes % 16) dst[units * 16 + threadIdx.x] = src[units * 16 + threadIdx.x];
+}
+
+// ---------------------------------------------------------------------------
 // Fused AdamW update + window pack.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
@@ -924,6 +942,17 @@ int launch_finalize(void* workspace, const void* parts, int nparts, const Finali
 int launch_gate(const uint64_t* released, uint64_t target, uint64_t max_ticks, uint32_t* timed_out, void* stream) {
     hipLaunchKernelGGL(gate_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(stream), released, target,
                        max_ticks, timed_out);
+    return static_cast<int>(hipGetLastError());
+}
+
+int launch_gather(const GatherArgs& a, int nseg, void* stream) {
+    if (nseg < 1 || nseg > kGatherSegs) return static_cast<int>(hipErrorInvalidValue);
+    uint64_t most = 0;
+    for (int k = 0; k < nseg; ++k) most = a.seg[k].bytes > most ? a.seg[k].bytes : most;
+    uint64_t blocks = (most / 16 + 4 * kBlock - 1) / (4 * kBlock);
+    blocks = blocks < 1 ? 1 : (blocks > kGatherBlocks ? kGatherBlocks : blocks);
+    hipLaunchKernelGGL(gather_kernel, dim3(static_cast<unsigned>(blocks), static_cast<unsigned>(nseg)), dim3(kBlock),
+                       0, static_cast<hipStream_t>(stream), a);
     return static_cast<int>(hipGetLastError());
 }
 

@@ -124,6 +124,7 @@ struct StepCopies {
     int first_after_kernel = 0;  // jobs before it need only the gradients
     int last_spill_g = -1, last_spill_s = -1, last_grad_job = -1;
     bool grads_ready_ev = false;  // ev_grads_ready was recorded for this step
+    bool gather = false;          // queued as one kernel, not copy by copy
 };
 
 // A staged copy: after `ev` its bytes are in `slot`; a worker moves them to
@@ -213,6 +214,7 @@ struct gockpt_ctx {
     int K = 0, s = 0;
     std::vector<int64_t> bounds;
     uint8_t* arena = nullptr;
+    uint8_t* arena_dev = nullptr;  // the pinned arena as a kernel sees it, or null
     size_t arena_bytes = 0;
     gockpt_arena_layout lay{};
     std::vector<uint64_t> goff;
@@ -309,7 +311,15 @@ struct gockpt_ctx {
     std::string persist_err;
     gockpt_io_stats persist_stats{};
 
-    // Every window copy goes through here.
+    // A gather counts as the copies it stands for.
+    bool gather_fails(const std::vector<Job>& jobs) {
+        if (fail_copy_at <= 0) return false;
+        int64_t n = 0;
+        for (const Job& j : jobs) n += static_cast<int64_t>((j.bytes + copy_bytes - 1) / copy_bytes);
+        const int64_t before = copies_issued.fetch_add(n);
+        return before < fail_copy_at && fail_copy_at <= before + n;
+    }
+    // Every other window copy goes through here.
     hipError_t copy_d2h(void* dst, const void* src, size_t bytes) {
         if (fail_copy_at > 0 && copies_issued.fetch_add(1) + 1 == fail_copy_at) return hipErrorInvalidValue;
         return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, xs);
@@ -934,6 +944,14 @@ int gockpt_begin_window_ex(gockpt_ctx* c, int K, const int64_t* bounds, void* ho
     c->lay = lay;
     c->goff = goff;
     c->staged = !pinned;
+    c->arena_dev = nullptr;
+    if (pinned) {
+        void* dev = nullptr;
+        if (hipHostGetDevicePointer(&dev, host_arena, 0) == hipSuccess)
+            c->arena_dev = static_cast<uint8_t*>(dev);
+        else
+            (void)hipGetLastError();
+    }
     c->R = R;
     c->wait_policy = policy;
     c->ring_off = opts != nullptr && opts->ring_off != 0;
@@ -1002,7 +1020,8 @@ int issue_copies(gockpt_ctx* c, StepCopies& d) {
     }
     // (the update leaves the gradient buffer as it was, so without the
     // gradients-ready event the update's event covers those copies too)
-    if ((e = hipStreamWaitEvent(c->xs, first_after_kernel > 0 && grads_ready_ev ? c->ev_grads_ready : c->ev_kernel,
+    if ((e = hipStreamWaitEvent(c->xs, first_after_kernel > 0 && grads_ready_ev && !d.gather ? c->ev_grads_ready
+                                                                                             : c->ev_kernel,
                                 0)) != hipSuccess)
         return c->hip_fail(e, "copy wait");
     if (timed && (e = hipEventRecord(tm.cp0, c->xs)) != hipSuccess) return c->hip_fail(e, "event record");
@@ -1017,7 +1036,28 @@ int issue_copies(gockpt_ctx* c, StepCopies& d) {
             return c->thread_fail();
         }
     }
-    for (size_t k = 0; k < jobs.size(); ++k) {
+    if (d.gather) {
+        GatherArgs ga{};
+        for (size_t k = 0; k < jobs.size(); ++k)
+            ga.seg[k] = {jobs[k].src, c->arena_dev + jobs[k].dst_off, jobs[k].bytes};
+        e = c->gather_fails(jobs) ? hipErrorInvalidValue
+                                  : static_cast<hipError_t>(launch_gather(ga, static_cast<int>(jobs.size()), c->xs));
+        if (e != hipSuccess) return c->hip_fail(e, "copy");
+        stt.n_copies++;
+        for (const Job& j : jobs) {
+            if (!j.ring) continue;
+            hipEvent_t ev = c->take_event();
+            if (ev == nullptr) return c->hip_fail(hipErrorOutOfMemory, "event create");
+            if ((e = hipEventRecord(ev, c->xs)) != hipSuccess) return c->hip_fail(e, "event record");
+            std::lock_guard<std::mutex> lk(c->mu);
+            j.ring->ev = ev;
+        }
+        if (last_spill_g >= 0 && (e = hipEventRecord(c->ev_grad_spill, c->xs)) != hipSuccess)
+            return c->hip_fail(e, "event record");
+        if (last_spill_s >= 0 && (e = hipEventRecord(c->ev_state_spill, c->xs)) != hipSuccess)
+            return c->hip_fail(e, "event record");
+    }
+    for (size_t k = 0; k < jobs.size() && !d.gather; ++k) {
         if (k > 0 && static_cast<int>(k) == first_after_kernel &&
             (e = hipStreamWaitEvent(c->xs, c->ev_kernel, 0)) != hipSuccess)
             return c->hip_fail(e, "copy wait");
@@ -1087,16 +1127,21 @@ int issue_copies(gockpt_ctx* c, StepCopies& d) {
             return c->hip_fail(e, "event record");
     }
     if (timed && (e = hipEventRecord(tm.cp1, c->xs)) != hipSuccess) return c->hip_fail(e, "event record");
-    if ((e = hipEventRecord(c->ev_last_copy, c->xs)) != hipSuccess) return c->hip_fail(e, "event record");
+    // the drain waits for the last step's, and WAIT_ALL for every step's
+    if ((s == c->K || c->wait_policy == GOCKPT_WAIT_ALL) && (e = hipEventRecord(c->ev_last_copy, c->xs)) != hipSuccess)
+        return c->hip_fail(e, "event record");
     // Explicit waits of the blocking schemes: the compute stream goes on
     // only once the step's gradients (or all of its copies) are on the host.
     if (c->wait_policy == GOCKPT_WAIT_GRADS && (e = hipStreamWaitEvent(c->cs, c->ev_grads_copied, 0)) != hipSuccess)
         return c->hip_fail(e, "wait for gradient copies");
     if (c->wait_policy == GOCKPT_WAIT_ALL && (e = hipStreamWaitEvent(c->cs, c->ev_last_copy, 0)) != hipSuccess)
         return c->hip_fail(e, "wait for the step's copies");
-    hipEvent_t done_ev = c->take_event();
-    if (done_ev == nullptr) return c->hip_fail(hipErrorOutOfMemory, "event create");
-    if ((e = hipEventRecord(done_ev, c->xs)) != hipSuccess) return c->hip_fail(e, "event record");
+    hipEvent_t done_ev = nullptr;  // the replayer of a direct window waits for it
+    if (c->R > 0 && !c->staged) {
+        done_ev = c->take_event();
+        if (done_ev == nullptr) return c->hip_fail(hipErrorOutOfMemory, "event create");
+        if ((e = hipEventRecord(done_ev, c->xs)) != hipSuccess) return c->hip_fail(e, "event record");
+    }
     {
         std::lock_guard<std::mutex> lk(c->mu);
         c->step_done[s] = done_ev;
@@ -1467,6 +1512,16 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     // first (Sec. 4.2.2).  Ring ranges are registered now, before the copies
     // are queued.
     int last_spill_g = -1, last_spill_s = -1;
+    // A small step's copies into a pinned arena go as one kernel, in the same
+    // place of the copy stream.  Under the other wait policies the gradients'
+    // copies are waited for by themselves, and the poison switch works on
+    // single copies.
+    uint64_t step_bytes = 0;
+    for (int k = 0; k < 4; ++k) step_bytes += static_cast<uint64_t>(seg_end[k] - seg_beg[k]) * (k == 0 ? 2 : 4);
+    const bool gather = c->arena_dev != nullptr && c->wait_policy == GOCKPT_WAIT_LAZY && !c->dbg_poison &&
+                        step_bytes <= kGatherMaxBytes;
+    const uint64_t piece = gather ? UINT64_MAX : c->copy_bytes;
+    RingCopy* gather_ring = nullptr;  // a gather's ring ranges share one entry
     auto emit_ring = [&](int k) {
         const uint64_t esz = k == 0 ? 2 : 4;
         const int64_t len = ring_end[k] - seg_beg[k];
@@ -1476,18 +1531,22 @@ int gockpt_step(gockpt_ctx* c, float lr) {
         // one bookkeeping entry per segment, its event recorded after the
         // segment's last copy: copies run in order, so that event covers the
         // whole segment (one event per segment, not per copy)
-        RingCopy* rcp;
-        {
+        RingCopy* rcp = nullptr;
+        if (gather_ring != nullptr) {
+            std::lock_guard<std::mutex> lk(c->mu);
+            gather_ring->lend = seg_lstart[k] + bytes;
+        } else {
             std::lock_guard<std::mutex> lk(c->mu);
             c->inflight.push_back({seg_lstart[k], seg_lstart[k] + bytes, nullptr});
             rcp = &c->inflight.back();
+            if (gather) gather_ring = rcp;
         }
         uint64_t lcur = seg_lstart[k], done = 0;
         while (done < bytes) {
             const uint64_t phys = lcur % R;
             uint64_t len_b = bytes - done;
             if (len_b > R - phys) len_b = R - phys;  // stop at the ring's end
-            if (len_b > c->copy_bytes) len_b = c->copy_bytes;
+            if (len_b > piece) len_b = piece;
             jobs.push_back({static_cast<uint8_t*>(cfg.ring) + phys, dst + done, len_b,
                             done + len_b == bytes ? rcp : nullptr, k == 0, true});
             done += len_b;
@@ -1508,7 +1567,7 @@ int gockpt_step(gockpt_ctx* c, float lr) {
         const uint64_t bytes = static_cast<uint64_t>(len) * esz;
         const uint64_t first = static_cast<uint64_t>(ring_end[k]) * esz;
         for (uint64_t done = 0; done < bytes;) {
-            const uint64_t len_b = bytes - done < c->copy_bytes ? bytes - done : c->copy_bytes;
+            const uint64_t len_b = bytes - done < piece ? bytes - done : piece;
             jobs.push_back({live[k] + first + done, dst_base[k] + first + done, len_b, nullptr, k == 0, false});
             done += len_b;
         }
@@ -1538,6 +1597,7 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     d.last_spill_s = last_spill_s;
     d.last_grad_job = last_grad_job;
     d.grads_ready_ev = grads_ready_ev;
+    d.gather = gather;
     stt.steps_done = s;
     c->s = s;
     if (s == c->K) c->st = WinState::Draining;

@@ -97,3 +97,18 @@ def test_one_launch_step_beside_a_full_device():
             assert np.array_equal(w, ref.w)
     if not any(beside):
         pytest.skip("the device ran the step after the other kernel each time")
+
+
+@pytest.mark.parametrize("case", ["ring", "spill", "no_ring", "host_wait"])
+def test_small_step_copies_in_one_kernel(case):
+    """A window step of at most 1 MiB sends its copies in one kernel, a larger
+    one by DMA: a window whose steps pass that size midway, with a ring that
+    holds a step, one that wraps and spills, none, and the HOST_WAIT plan with
+    a skipped step; odd lengths at the end."""
+    n = 262_147
+    kw = dict(ring=dict(ring_bytes=4 << 20, late_plan=2), spill=dict(ring_bytes=700 << 10, late_plan=2),
+              no_ring=dict(ring_bytes=0), host_wait=dict(ring_bytes=2 << 20, late_plan=1))[case]
+    _, stats, _ = _run_window(n, 4, [0, 65_536, 131_072, 196_608, n], seed=83, copy_bytes=64 << 10, dynamic=True,
+                              inf_steps=(3,), **kw)
+    pieces = -(-stats.bytes_d2h // (64 << 10))
+    assert 4 < stats.n_copies < pieces  # some steps as one kernel, some in 64 KiB copies
