@@ -192,6 +192,9 @@ struct FinalizeArgs {
 };
 
 // Launchers (gockpt_kernels.hip).  All stream-ordered, no host sync.
+// A new context's workspace: the loss-scaler state, and the words of the
+// one-launch step cleared.
+int launch_init(void* workspace, int64_t t, int64_t tracker, float scale, void* stream);
 int launch_prepass(const uint16_t* g, int64_t n, void* workspace, int nblocks, int nt, int grad_kind, void* stream);
 // parts: the partials to reduce (nparts of them, in order); raw: they hold
 // squares of the scaled gradients (bucket scans), which the finalize unscales.

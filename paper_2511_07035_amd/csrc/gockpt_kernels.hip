@@ -366,6 +366,19 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(uint8_t* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
+// The workspace of a new context, in one block (a caller's need not be
+// cleared, and the library's own holds what its last context left).
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void init_kernel(uint8_t* __restrict__ ws, int64_t t, int64_t tracker,
+                                                      float scale) {
+    uint32_t* words = reinterpret_cast<uint32_t*>(ws + kWsSlotsOff);
+    for (size_t i = threadIdx.x; i < (kWsStepEnd - kWsSlotsOff) / 4; i += kBlock) words[i] = 0u;
+    if (threadIdx.x != 0) return;
+    *reinterpret_cast<DevScaler*>(ws + kWsScalerOff) = DevScaler{t, tracker, scale, 0, {}};
+    *reinterpret_cast<StepSync*>(ws + kWsSyncOff) = StepSync{1u, 0u, {}};
+}
+
+// ---------------------------------------------------------------------------
 // Gate of the staged copies: the copy stream goes on once the host has moved
 // enough earlier copies out of their staging slots.  One wavefront polls the
 // host's counter (system-scope loads, never cached) and sleeps between polls;
@@ -942,6 +955,12 @@ int launch_finalize(void* workspace, const void* parts, int nparts, const Finali
 int launch_gate(const uint64_t* released, uint64_t target, uint64_t max_ticks, uint32_t* timed_out, void* stream) {
     hipLaunchKernelGGL(gate_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(stream), released, target,
                        max_ticks, timed_out);
+    return static_cast<int>(hipGetLastError());
+}
+
+int launch_init(void* workspace, int64_t t, int64_t tracker, float scale, void* stream) {
+    hipLaunchKernelGGL(init_kernel, dim3(1), dim3(kBlock), 0, static_cast<hipStream_t>(stream),
+                       static_cast<uint8_t*>(workspace), t, tracker, scale);
     return static_cast<int>(hipGetLastError());
 }
 

@@ -760,19 +760,8 @@ int create_ctx(const gockpt_config* cfg, uint8_t* ws, bool with_ctrl, gockpt_ctx
         }
     }
     if (he == hipSuccess) {
-        struct {
-            DevScaler sc;
-            StepSync sync;
-        } init{};
-        static_assert(offsetof(decltype(init), sync) == kWsSyncOff && kWsScalerOff == 0, "one upload");
-        init.sc.t = cfg->init_step;
-        init.sc.tracker = cfg->init_tracker;
-        init.sc.scale = cfg->init_scale;
-        init.sync.epoch = 1;
-        const std::vector<uint8_t> zero(kWsStepEnd - kWsSlotsOff, 0);
-        he = hipMemcpyAsync(c->ws + kWsScalerOff, &init, sizeof init, hipMemcpyHostToDevice, c->cs);
-        if (he == hipSuccess)
-            he = hipMemcpyAsync(c->ws + kWsSlotsOff, zero.data(), zero.size(), hipMemcpyHostToDevice, c->cs);
+        he = static_cast<hipError_t>(
+            launch_init(c->ws, cfg->init_step, cfg->init_tracker, cfg->init_scale, c->cs));
         if (he == hipSuccess) he = hipStreamSynchronize(c->cs);
     }
     if (he != hipSuccess) {
