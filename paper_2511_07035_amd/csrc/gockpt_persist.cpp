@@ -57,6 +57,27 @@ uint32_t crc32c(const uint8_t* p, uint64_t len) {
     return c32 ^ 0xFFFFFFFFu;
 }
 
+// CRCs of a message's blocks make the CRC of the whole.  Appending len bytes
+// to a message multiplies the polynomial its CRC stands for by x^(8 len)
+// modulo the generator; bit 31 of a CRC is the coefficient of x^0.
+uint32_t mul_mod(uint32_t a, uint32_t b) {
+    uint32_t r = 0;
+    for (int k = 0; k < 32; ++k) {
+        if (a & (0x80000000u >> k)) r ^= b;
+        b = (b >> 1) ^ (b & 1u ? 0x82F63B78u : 0u);  // times x; the Castagnoli generator
+    }
+    return r;
+}
+
+uint32_t x_pow_bytes(uint64_t len) {
+    uint32_t r = 0x80000000u, base = 0x00800000u;  // 1 and x^8
+    for (; len > 0; len >>= 1) {
+        if (len & 1u) r = mul_mod(r, base);
+        base = mul_mod(base, base);
+    }
+    return r;
+}
+
 struct Piece {
     int array;        // 0 master, 1 exp_avg, 2 exp_avg_sq
     uint64_t offset;  // byte offset inside the array
@@ -82,6 +103,23 @@ Layout make_layout(int64_t n, uint64_t piece) {
     }
     L.first.push_back(L.pieces.size());
     return L;
+}
+
+// Reading is shared out in blocks of a piece, so that few large pieces keep
+// every reader busy too.
+constexpr uint64_t kReadBlock = 1ull << 20;
+
+struct Block {
+    size_t piece;
+    uint64_t offset, bytes;  // inside the piece
+};
+
+std::vector<Block> read_blocks(const Layout& L) {
+    std::vector<Block> b;
+    for (size_t k = 0; k < L.pieces.size(); ++k)
+        for (uint64_t o = 0; o < L.pieces[k].bytes; o += kReadBlock)
+            b.push_back({k, o, L.pieces[k].bytes - o < kReadBlock ? L.pieces[k].bytes - o : kReadBlock});
+    return b;
 }
 
 int fail(int code, const std::string& msg) {
@@ -464,32 +502,38 @@ int gockpt_read_checkpoint(const char* dir, int64_t n, float* master, float* exp
     }
     uint8_t* dst[3] = {reinterpret_cast<uint8_t*>(master), reinterpret_cast<uint8_t*>(exp_avg),
                        reinterpret_cast<uint8_t*>(exp_avg_sq)};
-    std::atomic<int64_t> bad{-1};
+    // 100 MB in three pieces, with 16 readers: 5.5 ms by the piece, 2.9 by the
+    // block, most of it the copy out of the page cache
+    const std::vector<Block> blocks = read_blocks(L);
+    std::vector<uint32_t> crc(blocks.size());
     std::atomic<int> io_errno{0};  // errno is per thread: keep the reader's
-    const bool ok = parallel_pieces(L.pieces.size(), nthreads, [&](size_t k) {
-        const Piece& p = L.pieces[k];
-        uint8_t* d = dst[p.array] + p.offset;
-        if (!pread_all(fd, d, p.bytes, p.array * L.stride + p.offset)) {
+    const bool ok = parallel_pieces(blocks.size(), nthreads, [&](size_t k) {
+        const Block& b = blocks[k];
+        const Piece& p = L.pieces[b.piece];
+        uint8_t* d = dst[p.array] + p.offset + b.offset;
+        if (!pread_all(fd, d, b.bytes, p.array * L.stride + p.offset + b.offset)) {
             io_errno = errno;
             return false;
         }
-        const size_t idx = k - L.first[p.array];
-        if (crc32c(d, p.bytes) != m.crc[p.array][idx]) {
-            bad = static_cast<int64_t>(k);
-            return false;
-        }
+        crc[k] = crc32c(d, b.bytes);
         return true;
     });
     close(fd);
-    if (!ok) {
-        if (bad.load() >= 0) {
-            const Piece& p = L.pieces[static_cast<size_t>(bad.load())];
+    if (!ok)
+        return fail(GOCKPT_EFAILED, std::string("read_checkpoint: reading data.bin: ") +
+                                        (io_errno.load() ? strerror(io_errno.load()) : "short read"));
+    const uint32_t whole = x_pow_bytes(kReadBlock);
+    for (size_t k = 0; k < blocks.size();) {
+        const size_t piece = blocks[k].piece;
+        const Piece& p = L.pieces[piece];
+        uint32_t c = crc[k];
+        for (++k; k < blocks.size() && blocks[k].piece == piece; ++k)
+            c = mul_mod(blocks[k].bytes == kReadBlock ? whole : x_pow_bytes(blocks[k].bytes), c) ^ crc[k];
+        if (c != m.crc[p.array][piece - L.first[p.array]]) {
             const char* names[3] = {"master", "exp_avg", "exp_avg_sq"};
             return fail(GOCKPT_EFAILED, std::string("read_checkpoint: checksum mismatch in ") + names[p.array] +
                                             " at byte " + std::to_string(p.offset));
         }
-        return fail(GOCKPT_EFAILED, std::string("read_checkpoint: reading data.bin: ") +
-                                        (io_errno.load() ? strerror(io_errno.load()) : "short read"));
     }
     if (info != nullptr) to_info(m, info);
     if (stats != nullptr) {

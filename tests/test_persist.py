@@ -159,3 +159,32 @@ def test_bad_arguments(tmp_path):
         gockpt_read_checkpoint_info(str(tmp_path / "nowhere"))
     with pytest.raises(ValueError):
         gockpt_write_checkpoint(str(tmp_path / "y"), p, m[:50], v)
+
+
+@pytest.mark.parametrize("n", [262_143, 262_144, 262_145, 2 * 262_144, 700_001])
+def test_checksum_of_a_piece_read_in_blocks(tmp_path, n):
+    """A piece is read in 1 MiB blocks by several threads and its checksum put
+    together from theirs: around one, two and several blocks a piece, in one
+    piece and in pieces that end inside a block; a flipped bit in the first,
+    a middle or the last byte is found in its piece."""
+    for piece in (0, 1_536 << 10):
+        d = str(tmp_path / f"ck{piece}")
+        arrays = _arrays(n, n % 13)
+        gockpt_write_checkpoint(d, *arrays, piece_bytes=piece)
+        got = gockpt_read_checkpoint(d, n, nthreads=5)
+        for a, b in zip(arrays, got):
+            assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+        stride = (4 * n + 4095) // 4096 * 4096
+        for at in (0, 2 * n + 1, 4 * n - 1):
+            def flip():
+                with open(os.path.join(d, "data.bin"), "r+b") as f:
+                    f.seek(stride + at)
+                    byte = f.read(1)
+                    f.seek(stride + at)
+                    f.write(bytes([byte[0] ^ 0x01]))
+            flip()
+            first = at // piece * piece if piece else 0
+            with pytest.raises(GockptError, match=f"checksum mismatch in exp_avg at byte {first}$"):
+                gockpt_read_checkpoint(d, n)
+            flip()
+        gockpt_read_checkpoint(d, n)
