@@ -22,6 +22,7 @@ constexpr int kVec = 8;                 // elements per thread per group
 // 1721).  The prepass fills the device: one, two, four or eight loads are
 // within 1% from 8.4e6 elements on; below, two were 3% faster (2.1e6: 15.0,
 // 14.5, 15.0, 16.4 us a step).
+constexpr int64_t kCachedGradBytes = 512 << 20;  // read with the nontemporal hint above this
 constexpr int kPrepassAhead = 2;
 constexpr int kScanAhead = 4;
 constexpr int kPrepassMaxBlocks = 2048; // partial sums slots
@@ -171,7 +172,7 @@ struct GatherArgs {
 struct Knobs {
     int quads_per_thread;  // fused kernel: quads of 4 elements per thread
     int ring_nt;      // nontemporal ring stores
-    int prepass_nt;   // nontemporal gradient loads in the prepass
+    int prepass_nt;   // nontemporal gradient loads in the prepass and the scans; -1: by size
     int fused_nt;     // nontemporal loads and stores of the state in the fused kernel
     int fused_block;  // fused kernel threads per block: kFusedBlock (default) or kFusedWideBlock
     bool defaults;    // none of the above asked for otherwise

@@ -919,10 +919,10 @@ Knobs default_knobs() {
     Knobs k;
     k.quads_per_thread = env_int("GOCKPT_QUADS", 1);
     k.ring_nt = env_int("GOCKPT_RING_NT", 1);
-    k.prepass_nt = env_int("GOCKPT_PREPASS_NT", 1);
+    k.prepass_nt = env_int("GOCKPT_PREPASS_NT", -1);
     k.fused_nt = env_int("GOCKPT_FUSED_NT", 1);
     k.fused_block = env_int("GOCKPT_FUSED_BLOCK", 0);
-    k.defaults = k.quads_per_thread == 1 && k.ring_nt == 1 && k.prepass_nt == 1 && k.fused_nt == 1 &&
+    k.defaults = k.quads_per_thread == 1 && k.ring_nt == 1 && k.prepass_nt != 0 && k.fused_nt == 1 &&
                  k.fused_block != kFusedWideBlock;
     return k;
 }

@@ -727,6 +727,12 @@ int create_ctx(const gockpt_config* cfg, uint8_t* ws, bool with_ctrl, gockpt_ctx
     // 16-wavefront one (which cannot start on a compute unit another kernel
     // partly holds, so it slows down badly beside concurrent kernels)
     if (c->knobs.fused_block != kFusedWideBlock) c->knobs.fused_block = kFusedBlock;
+    // gradients that the last-level cache (256 MB) largely holds are read by
+    // the prepass and the scans without the nontemporal hint: the update then
+    // finds them there (us a step with and without it: 33.6e6 elements 157 and
+    // 151, 66e6 307 and 297, 124e6 574 and 555; 250e6 1157 and 1126..1166,
+    // from there on the same within 1%)
+    if (c->knobs.prepass_nt < 0) c->knobs.prepass_nt = 2 * cfg->n > kCachedGradBytes ? 1 : 0;
     if (const char* f = getenv("GOCKPT_TEST_FAIL_COPY")) c->fail_copy_at = atoll(f);
     auto env_on = [](const char* name) {
         const char* v = getenv(name);
