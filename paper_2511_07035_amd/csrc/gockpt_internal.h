@@ -61,10 +61,10 @@ struct alignas(256) StepArrive {
     uint32_t count;
 };
 constexpr int kStepArriveLanes = 16;
-constexpr int kStepMaxTiles = 256;  // a thread of a block reads one partial
-static_assert(kStepMaxTiles == kBlock, "one partial per thread");
+constexpr int kStepMaxTiles = 256;  // four partials a lane of the wavefront that reads them
+static_assert(kStepMaxTiles % 64 == 0, "whole rows of a wavefront");
 constexpr int64_t kStepMaxElems = int64_t{kStepMaxTiles} * 512 * 2 * 4 + 3;  // two quads a lane, and the tail
-constexpr int kStepHelpSpins = 32;  // polls (about 1 us each) before a block computes the partials it misses
+constexpr int kStepHelpSpins = 32;  // polls (0.5 to 1 us each) before a block computes the partials it misses
 
 static_assert(sizeof(gockpt_step_record) == 64, "record size");
 

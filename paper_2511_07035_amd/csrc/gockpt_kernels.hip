@@ -628,10 +628,12 @@ __global__ __launch_bounds__(kB) void fused_kernel(FusedArgs a) {
 // block keeps its tile in registers from the inf/NaN test to the update, and
 // the blocks exchange their partial sums through memory in between, so every
 // byte is read once.  Latency bounds it: the launch, one round of loads, the
-// exchange (about 1.5 us) and one round of stores.  Steps one after the other
-// on one stream, three launches against one: 11.0 us and 7.7 for 65560
-// elements, 11.4 and 9.0 for 524288, 11.1 and 10.2 for 1048579; without
-// anything to exchange 6.1, 6.8 and 8.3.
+// exchange (about 1.3 us) and one round of stores.  Steps one after the other
+// on one stream, three launches against one: 11.0 us and 7.6 for 65560
+// elements, 11.4 and 8.2 for 524288, 11.1 and 9.8 for 1048579; without
+// anything to exchange 6.2, 6.9 and 8.3.  The update's arithmetic runs before
+// the exchange and one wavefront polls for all: with the update after it and
+// a barrier per poll 7.8, 8.9 and 10.0.
 //
 // The exchange needs no block to be running beside another one.  A block that
 // has waited kStepHelpSpins polls for a partial computes the missing ones
@@ -660,8 +662,8 @@ __device__ __forceinline__ T ld_agent(const T* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Sum over the block, the same bits in every thread.  `lds` is not reused
-// before the next barrier but one.
+// Sum over the block, the same bits in every thread.  A barrier follows
+// before `lds` is used again.
 template <int kB>
 __device__ __forceinline__ double block_sum(double x, double* lds) {
     x = wave_sum(x);
@@ -742,8 +744,8 @@ template <bool kHasW, int kB, int kQ, int kKind, bool kJoint>
 __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, uint8_t* __restrict__ ws) {
     constexpr uint32_t kTile = kB * kQ * 4;
     __shared__ StepScalars s_sc;
-    __shared__ uint32_t s_epoch, s_found;
-    __shared__ double s_sum[2][kB / 64];
+    __shared__ uint32_t s_epoch, s_found, s_done;
+    __shared__ double s_sum[kB / 64], s_total;
     __shared__ uint8_t s_missing[kStepMaxTiles];
     const int tid = threadIdx.x;
     const int tiles = gridDim.x;
@@ -788,7 +790,7 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
 
     double mine = 0.0;
     if constexpr (kJoint)
-        mine = tile_sumsq<kB, kQ, kKind>(a, blockIdx.x, graw, s_sum[0]);
+        mine = tile_sumsq<kB, kQ, kKind>(a, blockIdx.x, graw, s_sum);
     else
         __syncthreads();
     const uint32_t epoch = s_epoch;
@@ -805,36 +807,59 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
     for (int h = 0; h < kQ; ++h) {
         update_quad<kKind>(s, graw[h], pv[h], mv[h], vv[h]);
         wv[h] = (u32x2){pack2_bf16(pv[h][0], pv[h][1]), pack2_bf16(pv[h][2], pv[h][3])};
+        asm volatile("" : "+v"(pv[h]), "+v"(mv[h]), "+v"(vv[h]), "+v"(wv[h]));  // here, not after the exchange
     }
 
     double acc = 0.0;
     if constexpr (kJoint) {
-        uint64_t word = 0;
-        bool have = tid >= tiles;
-        for (int spins = 0;; ++spins) {
-            if (!have) {
-                word = ld_agent(slots + tid);
-                have = (word & kSlotTagMask) == (epoch & kSlotTagMask);
-            }
-            if (__syncthreads_and(have)) break;
-            if (spins % kStepHelpSpins == kStepHelpSpins - 1) {
-                if (tid < kStepMaxTiles) s_missing[tid] = have ? 0 : 1;
-                __syncthreads();
-                for (int b = 0; b < tiles; ++b) {
-                    if (!s_missing[b]) continue;
-                    const double x = tile_sumsq<kB, kQ, kKind>(a, b, nullptr, s_sum[0]);
-                    if (tid == 0) publish(slots + b, epoch, x);
-                    __syncthreads();
+        // the first wavefront polls, a lane for every 64th partial
+        constexpr int kPer = kStepMaxTiles / 64;
+        for (;;) {
+            if (tid < 64) {
+                uint64_t word[kPer];
+                uint32_t missing = 0;  // bit k: this lane's k-th partial
+                for (int spins = 0; spins < kStepHelpSpins; ++spins) {
+                    missing = 0;
+#pragma unroll
+                    for (int k = 0; k < kPer; ++k) {
+                        const int b = tid + 64 * k;
+                        word[k] = b < tiles ? ld_agent(slots + b) : 0u;
+                    }
+#pragma unroll
+                    for (int k = 0; k < kPer; ++k)
+                        if (tid + 64 * k < tiles && (word[k] & kSlotTagMask) != (epoch & kSlotTagMask))
+                            missing |= 1u << k;
+                    if (__all(missing == 0u)) break;
+                }
+                if (__all(missing == 0u)) {
+                    double x = 0.0;
+#pragma unroll
+                    for (int k = 0; k < kPer; ++k) x += slot_value(word[k] & ~kSlotTagMask);
+                    x = wave_sum(x);
+                    if (tid == 0) s_total = x, s_done = 1u;
+                } else {
+#pragma unroll
+                    for (int k = 0; k < kPer; ++k) s_missing[tid + 64 * k] = (missing >> k) & 1u;
+                    if (tid == 0) s_done = 0u;
                 }
             }
+            __syncthreads();
+            if (__builtin_expect(s_done != 0u, 1)) break;
+            for (int b = 0; b < tiles; ++b) {
+                if (!s_missing[b]) continue;
+                const double x = tile_sumsq<kB, kQ, kKind>(a, b, nullptr, s_sum);
+                if (tid == 0) publish(slots + b, epoch, x);
+                __syncthreads();
+            }
+            __syncthreads();  // everyone has read s_done and s_missing
         }
-        acc = block_sum<kB>(tid < tiles ? slot_value(word) : 0.0, s_sum[1]);
+        acc = s_total;
     }
     uint32_t bad = (__builtin_bit_cast(uint64_t, acc) & 0x7FF0000000000000ull) == 0x7FF0000000000000ull ? 1u : 0u;
     if (fa.found_inf != nullptr) bad = s_found;
     const int skip = (fa.sc.check_overflow != 0 && bad != 0u) ? 1 : 0;
 
-    if (!skip) {
+    if (__builtin_expect(!skip, 1)) {
 #pragma unroll
         for (int h = 0; h < kQ; ++h) {
             const uint32_t o = o0 + h * (kB * 4u);
@@ -845,7 +870,7 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
             if (kHasW) *reinterpret_cast<u32x2*>(a.w + i0 + o) = wv[h];
         }
     }
-    if (a.pack.any) {
+    if (__builtin_expect(a.pack.any, 0)) {
         const TileSpan t = tile_span<kTile>(a, i0, skip);
         const bool packs_state = tile_packs_state(t);
         if (t.g_end != 0u || packs_state) {
@@ -864,7 +889,7 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
     }
     if (blockIdx.x == 0) update_tail<kHasW, kKind>(a, s, skip);
 
-    if (last) {
+    if (__builtin_expect(last, 0)) {
         for (int k = 0; k < kStepArriveLanes; ++k) lanes[k].count = 0u;
         sync->arrived = 0u;
         sync->epoch = in.epoch + 1u;
@@ -1036,9 +1061,9 @@ static int launch_step_q(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws
 template <int kKind, bool kJoint>
 static int launch_step_n(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, hipStream_t s) {
     const int64_t quads = a.n / 4, row = static_cast<int64_t>(kStepMaxTiles) * kBlock;
-    // at most 256 tiles, so that a thread polls one partial; beyond 256 rows of
-    // one quad per 256 threads, blocks of 512 (1.05e6 elements: 10.2 us with
-    // two quads a lane, 11.2 with 256 threads and four)
+    // at most 256 tiles, four partials a lane for the wavefront that polls;
+    // beyond 256 tiles of one quad a lane, blocks of 512 threads (1.05e6
+    // elements: two quads a lane 9% faster than 256 threads and four)
     if (quads <= row) return launch_step_q<kBlock, 1, kKind, kJoint>(a, fa, ws, s);
     if (quads <= 2 * row) return launch_step_q<2 * kBlock, 1, kKind, kJoint>(a, fa, ws, s);
     return launch_step_q<2 * kBlock, 2, kKind, kJoint>(a, fa, ws, s);

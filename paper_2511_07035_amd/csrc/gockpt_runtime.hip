@@ -1312,7 +1312,7 @@ int gockpt_step(gockpt_ctx* c, float lr) {
         !scanned && n > 0 && ((cfg.check_overflow != 0 && fin.found_inf == nullptr) || cfg.grad_norm_off == 0);
     // A small space takes the whole step in one launch (step_kernel), queued
     // where the update would be.  Up to kStepMaxElems, as far as its blocks
-    // hold their tiles in registers; there it is still the faster one (10.2 us
+    // hold their tiles in registers; there it is still the faster one (9.8 us
     // against 11.1).
     // Not with bucket scans (their partials are reduced by the finalize), nor
     // where the finalize has to end before the update is launched: the
