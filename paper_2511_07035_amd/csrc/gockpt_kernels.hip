@@ -58,12 +58,26 @@ __device__ __forceinline__ T ld_stream(const T* p) {
     else
         return *p;
 }
-template <bool kNT, class T>
-__device__ __forceinline__ void st_stream(T* p, T v) {
-    if constexpr (kNT)
-        __builtin_nontemporal_store(v, p);
-    else
-        *p = v;
+// A store of 8 or 16 bytes at a byte offset into a tile whose base is the same
+// for the whole block.  kThrough: beside the hint it is written through the L2
+// (sc1), so that no line waits there for its turn.  For the bandwidth-bound
+// shape; us a step with the hint alone and written through: 16.8e6 elements
+// 77.9 and 76.5, 33.6e6 151.5 and 149.5, 124e6 573 and 562, 350e6 1660 and
+// 1635, 1.63e9 the same within 0.5%.  Not for 2.1e6 elements, whose lines the
+// next step still finds in the L2: 17.1 and 17.9.
+template <bool kNT, bool kThrough, uint32_t kTileBytes, class T>
+__device__ __forceinline__ void st_tile(void* base, uint32_t off, T v) {
+    static_assert(sizeof(T) == 16 || sizeof(T) == 8, "8 or 16 bytes");
+    if constexpr (!kNT) {
+        *reinterpret_cast<T*>(static_cast<uint8_t*>(base) + off) = v;
+    } else {
+        constexpr int kBits = kThrough ? 2 | 16 : 2;  // nt, sc1
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(base, 0, kTileBytes, 0x00020000);
+        if constexpr (sizeof(T) == 16)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rsrc, off, 0, kBits);
+        else
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rsrc, off, 0, kBits);
+    }
 }
 
 // Ring stores: the ring is only read back by the copy engine, so bypass the
@@ -574,12 +588,12 @@ __global__ __launch_bounds__(kB) void fused_kernel(FusedArgs a) {
         for (int h = 0; h < kQ; ++h) {
             const uint32_t o = o0 + h * (kB * 4u);
             update_quad<kKind>(s, graw[h], pv[h], mv[h], vv[h]);
-            st_stream<kNT>(reinterpret_cast<f32x4*>(pt + o), pv[h]);
-            st_stream<kNT>(reinterpret_cast<f32x4*>(mt + o), mv[h]);
-            st_stream<kNT>(reinterpret_cast<f32x4*>(vt + o), vv[h]);
+            st_tile<kNT, kB == kFusedBlock, kTile * 4>(pt, o * 4u, pv[h]);
+            st_tile<kNT, kB == kFusedBlock, kTile * 4>(mt, o * 4u, mv[h]);
+            st_tile<kNT, kB == kFusedBlock, kTile * 4>(vt, o * 4u, vv[h]);
             if (kHasW) {
                 const u32x2 wv = {pack2_bf16(pv[h][0], pv[h][1]), pack2_bf16(pv[h][2], pv[h][3])};
-                st_stream<kNT>(reinterpret_cast<u32x2*>(wt + o), wv);
+                st_tile<kNT, kB == kFusedBlock, kTile * 2>(wt, o * 2u, wv);
             }
         }
         if (a.pack.any) {
@@ -606,12 +620,12 @@ __global__ __launch_bounds__(kB) void fused_kernel(FusedArgs a) {
             vv[h] = ld_stream<kNT>(reinterpret_cast<const f32x4*>(vt + o));
             if (!skip) {
                 update_quad<kKind>(s, graw[h], pv[h], mv[h], vv[h]);
-                st_stream<kNT>(reinterpret_cast<f32x4*>(pt + o), pv[h]);
-                st_stream<kNT>(reinterpret_cast<f32x4*>(mt + o), mv[h]);
-                st_stream<kNT>(reinterpret_cast<f32x4*>(vt + o), vv[h]);
+                st_tile<kNT, kB == kFusedBlock, kTile * 4>(pt, o * 4u, pv[h]);
+                st_tile<kNT, kB == kFusedBlock, kTile * 4>(mt, o * 4u, mv[h]);
+                st_tile<kNT, kB == kFusedBlock, kTile * 4>(vt, o * 4u, vv[h]);
                 if (kHasW) {
                     const u32x2 wv = {pack2_bf16(pv[h][0], pv[h][1]), pack2_bf16(pv[h][2], pv[h][3])};
-                    st_stream<kNT>(reinterpret_cast<u32x2*>(wt + o), wv);
+                    st_tile<kNT, kB == kFusedBlock, kTile * 2>(wt, o * 2u, wv);
                 }
             }
             pack_quad(a.pack, t, i0, o, graw[h], pv[h], mv[h], vv[h]);
