@@ -522,8 +522,8 @@ int gockpt_scan_grads(gockpt_ctx* ctx, int64_t begin, int64_t end, void* stream)
  * Inside a window, window step s packs part s of the updated state and the
  * gradients of parts 1..s-1 and queues their copies to the host arena on the
  * copy stream; after the K-th step the window is DRAINING.  Outside a window
- * it is the plain fused update: three kernels on the compute stream (one for
- * small spaces) and no host-side decision, so it may be captured in a HIP
+ * it is the plain fused update: one to three kernels on the compute stream
+ * (by size and options) and no host-side decision, so it may be captured in a HIP
  * graph (stream capture of the compute stream) and replayed; lr is fixed at
  * capture, while the step count and the loss scale live on the device and
  * advance with every replay.

@@ -64,6 +64,9 @@ constexpr int kStepArriveLanes = 16;
 constexpr int kStepMaxTiles = 256;  // four partials a lane of the wavefront that reads them
 static_assert(kStepMaxTiles % 64 == 0, "whole rows of a wavefront");
 constexpr int64_t kStepMaxElems = int64_t{kStepMaxTiles} * 512 * 2 * 4 + 3;  // two quads a lane, and the tail
+// Steps in one launch behind a prepass or bucket scans, or with nothing to sum.
+constexpr int64_t kAfterMaxElems = int64_t{1} << 22;
+constexpr int kAfterMaxParts = 512;  // partials every block then reduces: 8 KiB from the L2
 constexpr int kStepHelpSpins = 32;  // polls (0.5 to 1 us each) before a block computes the partials it misses
 
 static_assert(sizeof(gockpt_step_record) == 64, "record size");
@@ -210,9 +213,11 @@ int launch_scan(const uint16_t* g, int64_t begin, int64_t end, void* parts, int 
                 void* stream);
 int scan_blocks_for(int64_t count, int max_blocks);
 int launch_fused(const FusedArgs& a, void* stream);
-// The whole step in one launch: 1 <= n <= kStepMaxElems; joint: it tests the
-// gradients or sums their squares.
-int launch_step(const FusedArgs& a, const FinalizeArgs& fin, bool joint, void* workspace, void* stream);
+// The step in one launch (see step_kernel).  kStepJoint: 1 <= n <=
+// kStepMaxElems; the others: 1 <= n <= kAfterMaxElems, parts with kStepAfter.
+enum StepMode : int { kStepAlone = 0, kStepJoint = 1, kStepAfter = 2 };
+int launch_step(const FusedArgs& a, const FinalizeArgs& fin, int mode, void* workspace, const void* parts, int nparts,
+                void* stream);
 int prepass_blocks_for(int64_t n);
 Knobs default_knobs();
 

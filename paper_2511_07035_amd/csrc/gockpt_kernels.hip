@@ -16,6 +16,10 @@
 //                    decision to the host).
 //   gate_kernel      one wavefront on the copy stream that waits until the
 //                    host has emptied a staging slot before a copy reuses it.
+//   step_kernel      a small space's whole step in one launch, or its end
+//                    (finalize and update) behind a prepass or bucket scans.
+//   gather_kernel    the copies of a small window step to pinned host memory.
+//   init_kernel      the workspace of a new context.
 //   fused_kernel     the mixed-precision AdamW update of every element
 //                    (Sec. 2.2, AdamW of Sec. 4.3.1) fused with the window's
 //                    pack (Sec. 4.2.1): the step's part of the updated state
@@ -752,14 +756,23 @@ __device__ __forceinline__ bool arrive_last(StepSync* sync, StepArrive* lanes, i
     return __hip_atomic_fetch_add(&sync->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == used;
 }
 
-// kJoint: the step needs the sum over all gradients (overflow test or norm);
-// without it nothing is exchanged.
-template <bool kHasW, int kB, int kQ, int kKind, bool kJoint>
-__global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, uint8_t* __restrict__ ws) {
+// kStepJoint: the step needs the sum over all gradients (overflow test or
+// norm) and takes it itself.  kStepAfter: a prepass or bucket scans before it
+// have left their partials (at most kAfterMaxParts), which every block reduces
+// for itself instead of waiting for a finalize launch; kStepAlone: nothing is
+// summed.  These two exchange nothing, so they may have more blocks than the
+// device has places, and go up to kAfterMaxElems, where the separate kernels'
+// shape changes.  us a step with a finalize launch and without: behind a
+// prepass 2.1e6 elements 17.1 and 14.2, 4.2e6 27.6 and 25.4 (1.05e6 the same);
+// alone 13.4 and 10.6, 22.1 and 20.7; behind 4 bucket scans 100 and 89.
+template <bool kHasW, int kB, int kQ, int kKind, int kMode>
+__global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, uint8_t* __restrict__ ws,
+                                                  const Partial* __restrict__ parts, int nparts) {
     constexpr uint32_t kTile = kB * kQ * 4;
     __shared__ StepScalars s_sc;
     __shared__ uint32_t s_epoch, s_found, s_done;
     __shared__ double s_sum[kB / 64], s_total;
+    __shared__ uint32_t s_bad[kB / 64];
     __shared__ uint8_t s_missing[kStepMaxTiles];
     const int tid = threadIdx.x;
     const int tiles = gridDim.x;
@@ -802,14 +815,26 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
         s_sc = step_scalars(fa.hp, fa.lr, in.st.t + 1, in.st.scale);
     }
 
-    double mine = 0.0;
-    if constexpr (kJoint)
-        mine = tile_sumsq<kB, kQ, kKind>(a, blockIdx.x, graw, s_sum);
-    else
+    double acc = 0.0;
+    uint32_t bad = 0u;
+    if constexpr (kMode == kStepJoint) {
+        acc = tile_sumsq<kB, kQ, kKind>(a, blockIdx.x, graw, s_sum);
+    } else if constexpr (kMode == kStepAfter) {
+        for (int b = tid; b < nparts; b += kB) {
+            acc += parts[b].sumsq;
+            bad |= static_cast<uint32_t>(parts[b].nonfinite);
+        }
+        bad = __any(bad != 0u) ? 1u : 0u;
+        if ((tid & 63) == 0) s_bad[tid >> 6] = bad;
+        acc = block_sum<kB>(acc, s_sum);
+#pragma unroll
+        for (int w = 0; w < kB / 64; ++w) bad |= s_bad[w];
+    } else {
         __syncthreads();
+    }
     const uint32_t epoch = s_epoch;
     if (tid == 0) {
-        if (kJoint) publish(slots + blockIdx.x, epoch, mine);
+        if (kMode == kStepJoint) publish(slots + blockIdx.x, epoch, acc);
         last = arrive_last(sync, lanes, tiles);
     }
 
@@ -824,8 +849,7 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
         asm volatile("" : "+v"(pv[h]), "+v"(mv[h]), "+v"(vv[h]), "+v"(wv[h]));  // here, not after the exchange
     }
 
-    double acc = 0.0;
-    if constexpr (kJoint) {
+    if constexpr (kMode == kStepJoint) {
         // the first wavefront polls, a lane for every 64th partial
         constexpr int kPer = kStepMaxTiles / 64;
         for (;;) {
@@ -868,8 +892,8 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
             __syncthreads();  // everyone has read s_done and s_missing
         }
         acc = s_total;
+        bad = (__builtin_bit_cast(uint64_t, acc) & 0x7FF0000000000000ull) == 0x7FF0000000000000ull ? 1u : 0u;
     }
-    uint32_t bad = (__builtin_bit_cast(uint64_t, acc) & 0x7FF0000000000000ull) == 0x7FF0000000000000ull ? 1u : 0u;
     if (fa.found_inf != nullptr) bad = s_found;
     const int skip = (fa.sc.check_overflow != 0 && bad != 0u) ? 1 : 0;
 
@@ -906,7 +930,7 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
     if (__builtin_expect(last, 0)) {
         for (int k = 0; k < kStepArriveLanes; ++k) lanes[k].count = 0u;
         sync->arrived = 0u;
-        sync->epoch = in.epoch + 1u;
+        if (kMode == kStepJoint) sync->epoch = in.epoch + 1u;
         finish_step(ws, fa, in.st, acc, bad);
     }
 }
@@ -1049,46 +1073,65 @@ static int launch_fused_nt(const FusedArgs& a, hipStream_t s) {
         case 2: return launch_fused_q<2, kKind, kNT, kFusedBlock>(a, s);
         default:
             if (a.block == kFusedWideBlock) return launch_fused_q<1, kKind, kNT, kFusedWideBlock>(a, s);
-            // up to two rounds of all wave slots (4.2e6 elements) latency
-            // bounds the launch: four times fewer blocks to start, and no
-            // residency limit (1.05e6 elements: 8.8 us a step with 256
-            // threads a block, 10.7 with 64; 8.4e6: 44.2 against 40.7)
+            // up to two rounds of all wave slots (4.2e6 elements; steps that
+            // step_kernel does not take) latency bounds the launch: four times
+            // fewer blocks to start, and no residency limit (1.05e6 elements:
+            // 8.8 us a step with 256 threads a block, 10.7 with 64; 8.4e6:
+            // 44.2 against 40.7)
             return a.n <= 2 * kWaveSlots * int64_t{256} ? launch_fused_q<1, kKind, kNT, kBlock>(a, s)
                                                         : launch_fused_q<1, kKind, kNT, kFusedBlock>(a, s);
     }
 }
 
-template <int kB, int kQ, int kKind, bool kJoint>
-static int launch_step_q(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, hipStream_t s) {
+template <int kB, int kQ, int kKind, int kMode>
+static int launch_step_q(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, const Partial* parts, int nparts,
+                         hipStream_t s) {
     const int64_t per_block = static_cast<int64_t>(kB) * kQ * 4;
     int64_t tiles = (a.n / 4 * 4 + per_block - 1) / per_block;
     if (tiles < 1) tiles = 1;
-    if (tiles > kStepMaxTiles) return static_cast<int>(hipErrorInvalidValue);
+    if (kMode == kStepJoint && tiles > kStepMaxTiles) return static_cast<int>(hipErrorInvalidValue);
     const unsigned grid = static_cast<unsigned>(tiles);
     if (a.w != nullptr)
-        hipLaunchKernelGGL((step_kernel<true, kB, kQ, kKind, kJoint>), dim3(grid), dim3(kB), 0, s, a, fa, ws);
+        hipLaunchKernelGGL((step_kernel<true, kB, kQ, kKind, kMode>), dim3(grid), dim3(kB), 0, s, a, fa, ws, parts,
+                           nparts);
     else
-        hipLaunchKernelGGL((step_kernel<false, kB, kQ, kKind, kJoint>), dim3(grid), dim3(kB), 0, s, a, fa, ws);
+        hipLaunchKernelGGL((step_kernel<false, kB, kQ, kKind, kMode>), dim3(grid), dim3(kB), 0, s, a, fa, ws, parts,
+                           nparts);
     return static_cast<int>(hipGetLastError());
 }
 
-template <int kKind, bool kJoint>
-static int launch_step_n(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, hipStream_t s) {
+template <int kKind, int kMode>
+static int launch_step_n(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, const Partial* parts, int nparts,
+                         hipStream_t s) {
     const int64_t quads = a.n / 4, row = static_cast<int64_t>(kStepMaxTiles) * kBlock;
-    // at most 256 tiles, four partials a lane for the wavefront that polls;
-    // beyond 256 tiles of one quad a lane, blocks of 512 threads (1.05e6
-    // elements: two quads a lane 9% faster than 256 threads and four)
-    if (quads <= row) return launch_step_q<kBlock, 1, kKind, kJoint>(a, fa, ws, s);
-    if (quads <= 2 * row) return launch_step_q<2 * kBlock, 1, kKind, kJoint>(a, fa, ws, s);
-    return launch_step_q<2 * kBlock, 2, kKind, kJoint>(a, fa, ws, s);
+    // at most 256 tiles for the exchange, four partials a lane for the
+    // wavefront that polls; beyond 256 tiles of one quad a lane, blocks of 512
+    // threads (1.05e6 elements: two quads a lane 9% faster than 256 threads
+    // and four)
+    if (quads <= row) return launch_step_q<kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, s);
+    if (quads <= 2 * row) return launch_step_q<2 * kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, s);
+    return launch_step_q<2 * kBlock, 2, kKind, kMode>(a, fa, ws, parts, nparts, s);
 }
 
-int launch_step(const FusedArgs& a, const FinalizeArgs& fin, bool joint, void* workspace, void* stream) {
+template <int kKind>
+static int launch_step_kind(const FusedArgs& a, const FinalizeArgs& fa, int mode, uint8_t* ws, const Partial* parts,
+                            int nparts, hipStream_t s) {
+    switch (mode) {
+        case kStepJoint: return launch_step_n<kKind, kStepJoint>(a, fa, ws, parts, nparts, s);
+        case kStepAfter: return launch_step_n<kKind, kStepAfter>(a, fa, ws, parts, nparts, s);
+        default: return launch_step_n<kKind, kStepAlone>(a, fa, ws, parts, nparts, s);
+    }
+}
+
+int launch_step(const FusedArgs& a, const FinalizeArgs& fin, int mode, void* workspace, const void* parts, int nparts,
+                void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    if (a.grad_kind == kGradFP16)
-        return joint ? launch_step_n<kGradFP16, true>(a, fin, ws, s) : launch_step_n<kGradFP16, false>(a, fin, ws, s);
-    return joint ? launch_step_n<kGradBF16, true>(a, fin, ws, s) : launch_step_n<kGradBF16, false>(a, fin, ws, s);
+    const Partial* p = static_cast<const Partial*>(parts);
+    if (a.n < 1 || a.n > (mode == kStepJoint ? kStepMaxElems : kAfterMaxElems))
+        return static_cast<int>(hipErrorInvalidValue);
+    return a.grad_kind == kGradFP16 ? launch_step_kind<kGradFP16>(a, fin, mode, ws, p, nparts, s)
+                                    : launch_step_kind<kGradBF16>(a, fin, mode, ws, p, nparts, s);
 }
 
 template <int kKind>

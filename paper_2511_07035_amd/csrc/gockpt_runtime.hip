@@ -1310,19 +1310,22 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     const bool scanned = !c->scan_ranges.empty();
     const bool prepass =
         !scanned && n > 0 && ((cfg.check_overflow != 0 && fin.found_inf == nullptr) || cfg.grad_norm_off == 0);
-    // A small space takes the whole step in one launch (step_kernel), queued
-    // where the update would be.  Up to kStepMaxElems, as far as its blocks
-    // hold their tiles in registers; there it is still the faster one (9.8 us
-    // against 11.1).
-    // Not with bucket scans (their partials are reduced by the finalize), nor
-    // where the finalize has to end before the update is launched: the
+    // Small spaces end the step in the launch that updates (step_kernel),
+    // queued where the update would be: up to kStepMaxElems it tests and sums
+    // the gradients too, as far as its blocks hold their tiles in registers
+    // (there it is still the faster one, 9.8 us against 11.1); up to
+    // kAfterMaxElems it reduces the partials of the prepass or the scans.
+    // Not where the finalize has to end before the update is launched: the
     // HOST_WAIT plan reads its decision, and timing events stand around both.
     // The launch-shape knobs belong to the separate kernels.
-    const bool one_launch = n > 0 && n <= kStepMaxElems && !scanned && !timed && c->knobs.defaults &&
+    const bool one_launch = n > 0 && n <= kAfterMaxElems && !timed && c->knobs.defaults &&
+                            !(scanned && c->scan_used > kAfterMaxParts) &&
                             !(in_window && c->ring_plan == GOCKPT_RING_HOST_WAIT && R);
-    if (prepass && !one_launch) {
+    const int step_mode = scanned || (prepass && n > kStepMaxElems) ? kStepAfter : (prepass ? kStepJoint : kStepAlone);
+    const int pre_blocks = one_launch && c->pre_blocks > kAfterMaxParts ? kAfterMaxParts : c->pre_blocks;
+    if (prepass && !(one_launch && step_mode == kStepJoint)) {
         e = static_cast<hipError_t>(
-            launch_prepass(cfg.grad16, n, c->ws, c->pre_blocks, c->knobs.prepass_nt, cfg.grad_dtype, c->cs));
+            launch_prepass(cfg.grad16, n, c->ws, pre_blocks, c->knobs.prepass_nt, cfg.grad_dtype, c->cs));
         if (e != hipSuccess) return c->hip_fail(e, "prepass launch");
     }
     for (const auto& se : c->scan_events)
@@ -1331,10 +1334,11 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     const uint8_t* parts = c->ws + (scanned ? kWsScanOff + static_cast<size_t>(c->scan_bank) * kScanSlots *
                                                                sizeof(Partial)
                                             : kWsPartialsOff);
-    fin.raw = scanned || one_launch ? 1 : 0;
+    const int nparts = scanned ? c->scan_used : (prepass ? pre_blocks : 0);
+    fin.raw = scanned || (one_launch && step_mode == kStepJoint) ? 1 : 0;
     if (!one_launch) {
         e = static_cast<hipError_t>(
-            launch_finalize(c->ws, parts, scanned ? c->scan_used : (prepass ? c->pre_blocks : 0), fin, c->cs));
+            launch_finalize(c->ws, parts, nparts, fin, c->cs));
         if (e != hipSuccess) return c->hip_fail(e, "finalize launch");
     }
     if (scanned) {  // the next step's scans fill the other bank
@@ -1484,7 +1488,7 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     }
     if (timed && (e = hipEventRecord(tm.upd0, c->cs)) != hipSuccess) return c->hip_fail(e, "event record");
     if (one_launch) {
-        if ((e = static_cast<hipError_t>(launch_step(a, fin, prepass, c->ws, c->cs))) != hipSuccess)
+        if ((e = static_cast<hipError_t>(launch_step(a, fin, step_mode, c->ws, parts, nparts, c->cs))) != hipSuccess)
             return c->hip_fail(e, "step launch");
     } else if (n > 0) {
         if ((e = static_cast<hipError_t>(launch_fused(a, c->cs))) != hipSuccess) return c->hip_fail(e, "fused launch");

@@ -112,3 +112,25 @@ def test_small_step_copies_in_one_kernel(case):
                               inf_steps=(3,), **kw)
     pieces = -(-stats.bytes_d2h // (64 << 10))
     assert 4 < stats.n_copies < pieces  # some steps as one kernel, some in 64 KiB copies
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(grad_dtype="fp16"), dict(grad_norm=False, found_inf=[0.0, 1.0, 0.0]),
+                                dict(check_overflow=False, grad_norm=False, with_weight=False)])
+def test_step_behind_a_prepass_or_alone(kw):
+    """Between the one-launch sizes and 2^22 the launch that updates also
+    reduces the prepass's partials, or has nothing to reduce."""
+    n = 2_000_003
+    inf = dict(dynamic=True, inf_steps=(3,)) if kw.get("check_overflow", True) and "found_inf" not in kw else {}
+    _, stats, _ = _run_window(n, 3, [0, 600_000, 1_400_008, n], seed=67, ring_bytes=6 << 20, late_plan=2, **inf, **kw)
+    assert stats.skipped == (1 if inf or "found_inf" in kw else 0)
+
+
+@pytest.mark.parametrize("buckets", [1, 7, 512, 600])
+def test_step_behind_bucket_scans(buckets):
+    """Up to 512 partials of bucket scans are reduced by the launch that
+    updates, more by a finalize of their own; with a skipped step."""
+    n = 700_003
+    ends = [n * k // buckets // 8 * 8 for k in range(buckets)] + [n]
+    _, stats, _ = _run_window(n, 4, [0, 200_000, 400_000, 600_000, n], seed=73, ring_bytes=4 << 20, dynamic=True,
+                              inf_steps=(3,), scan_buckets=ends, per_step=False)
+    assert stats.skipped == 1
