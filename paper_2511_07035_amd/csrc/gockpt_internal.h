@@ -75,9 +75,10 @@ static_assert(sizeof(gockpt_step_record) == 64, "record size");
 // [prepass partials][bucket-scan partials: two banks, alternating by step,
 // so the scans of the next step never overwrite what this step's finalize
 // still has to read]
-// The one-launch step keeps its sync words in the first pad and its slots in
-// the second half of the prepass partials: a space small enough for it has
-// at most kStepMaxElems / (kVec * kBlock) prepass blocks.
+// The one-launch step keeps its sync words in the first pad, and its slots and
+// counters in the second half of the prepass partials: a space of at most
+// kAfterMaxElems, whatever form its steps take, has at most kAfterMaxParts
+// prepass blocks (prepass_blocks_for).
 constexpr size_t kWsScalerOff = 0;
 constexpr size_t kWsSyncOff = 64;
 constexpr size_t kWsRecordsOff = 256;
@@ -89,7 +90,19 @@ constexpr size_t kWsArriveOff = kWsSlotsOff + kStepMaxTiles * sizeof(uint64_t);
 constexpr size_t kWsStepEnd = kWsArriveOff + kStepArriveLanes * sizeof(StepArrive);
 static_assert(kWsSyncOff + sizeof(StepSync) <= kWsRecordsOff, "sync words");
 static_assert(kWsArriveOff % 256 == 0 && kWsStepEnd <= kWsScanOff, "slots and counters");
-static_assert(kStepMaxElems / (kVec * kBlock) + 1 <= kPrepassMaxBlocks / 2, "slots beside the partials");
+
+// Blocks of the prepass, one group of a lane each as far as they go.  Up to
+// kAfterMaxElems at most kAfterMaxParts, also where a finalize of its own
+// reduces them (HOST_WAIT, timed windows): another step of the same context
+// ends in one launch, and its counters lie behind these partials.
+constexpr int prepass_blocks_for(int64_t n) {
+    const int64_t most = n <= kAfterMaxElems ? kAfterMaxParts : kPrepassMaxBlocks;
+    const int64_t b = (n / kVec + kBlock - 1) / kBlock;
+    return static_cast<int>(b < 1 ? 1 : (b > most ? most : b));
+}
+static_assert(kWsPartialsOff + prepass_blocks_for(kAfterMaxElems) * sizeof(Partial) <= kWsSlotsOff &&
+                  kStepMaxElems <= kAfterMaxElems,
+              "slots and counters beside the partials");
 constexpr size_t kWsBytes = kWsScanOff + 2 * kScanSlots * sizeof(Partial);
 
 // Page-locked, host-coherent control page of a context (4 KiB).  The device
@@ -218,7 +231,6 @@ int launch_fused(const FusedArgs& a, void* stream);
 enum StepMode : int { kStepAlone = 0, kStepJoint = 1, kStepAfter = 2 };
 int launch_step(const FusedArgs& a, const FinalizeArgs& fin, int mode, void* workspace, const void* parts, int nparts,
                 void* stream);
-int prepass_blocks_for(int64_t n);
 Knobs default_knobs();
 
 }  // namespace gockpt

@@ -944,14 +944,6 @@ static int env_int(const char* name, int dflt) {
     return atoi(s);
 }
 
-int prepass_blocks_for(int64_t n) {
-    const int64_t groups = n / kVec;
-    int64_t b = (groups + kBlock - 1) / kBlock;
-    if (b < 1) b = 1;
-    if (b > kPrepassMaxBlocks) b = kPrepassMaxBlocks;
-    return static_cast<int>(b);
-}
-
 int scan_blocks_for(int64_t count, int max_blocks) {
     // at least four 8-element groups per lane
     int64_t b = (count / kVec + 4 * kBlock - 1) / (4 * kBlock);

@@ -1322,10 +1322,9 @@ int gockpt_step(gockpt_ctx* c, float lr) {
                             !(scanned && c->scan_used > kAfterMaxParts) &&
                             !(in_window && c->ring_plan == GOCKPT_RING_HOST_WAIT && R);
     const int step_mode = scanned || (prepass && n > kStepMaxElems) ? kStepAfter : (prepass ? kStepJoint : kStepAlone);
-    const int pre_blocks = one_launch && c->pre_blocks > kAfterMaxParts ? kAfterMaxParts : c->pre_blocks;
     if (prepass && !(one_launch && step_mode == kStepJoint)) {
         e = static_cast<hipError_t>(
-            launch_prepass(cfg.grad16, n, c->ws, pre_blocks, c->knobs.prepass_nt, cfg.grad_dtype, c->cs));
+            launch_prepass(cfg.grad16, n, c->ws, c->pre_blocks, c->knobs.prepass_nt, cfg.grad_dtype, c->cs));
         if (e != hipSuccess) return c->hip_fail(e, "prepass launch");
     }
     for (const auto& se : c->scan_events)
@@ -1334,7 +1333,7 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     const uint8_t* parts = c->ws + (scanned ? kWsScanOff + static_cast<size_t>(c->scan_bank) * kScanSlots *
                                                                sizeof(Partial)
                                             : kWsPartialsOff);
-    const int nparts = scanned ? c->scan_used : (prepass ? pre_blocks : 0);
+    const int nparts = scanned ? c->scan_used : (prepass ? c->pre_blocks : 0);
     fin.raw = scanned || (one_launch && step_mode == kStepJoint) ? 1 : 0;
     if (!one_launch) {
         e = static_cast<hipError_t>(

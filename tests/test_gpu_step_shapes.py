@@ -134,3 +134,80 @@ def test_step_behind_bucket_scans(buckets):
     _, stats, _ = _run_window(n, 4, [0, 200_000, 400_000, 600_000, n], seed=73, ring_bytes=4 << 20, dynamic=True,
                               inf_steps=(3,), scan_buckets=ends, per_step=False)
     assert stats.skipped == 1
+
+
+@pytest.mark.parametrize("n", [2_383_872, 2_383_880, 3_000_003, 4_194_304])
+@pytest.mark.parametrize("scan_first", [False, True])
+def test_launch_forms_mixed_in_one_context(n, scan_first):
+    """Plain steps end in one launch, HOST_WAIT and timed windows take the
+    separate kernels; one context runs both in turn over one workspace.  At
+    the sizes where the separate prepass, left to itself, would reach the
+    one-launch step's counters: the step count, loss scale and growth tracker,
+    the records, the device state and every restored checkpoint are the
+    oracle's after each stretch."""
+    import numpy as np
+
+    import oracle
+    import synth
+    from gpu_util import assert_bits_equal, load_state, to_device_grad16
+    from paper_2511_07035_amd import Session
+
+    cfg = oracle.AdamWConfig(dynamic_scale=True, init_scale=1024.0, growth_interval=4)
+    p0 = synth.master_cpu(n, 91)
+    ref = oracle.State(p0, scale=1024.0)
+    good = [synth.grads_cpu(n, 91, s, scale=1024.0) for s in (1, 2)]
+    inf = synth.grads_cpu(n, 91, 3, scale=1024.0, plant_inf=True)
+    K = 3
+    bounds = [0, n // 3 // 8 * 8, 2 * n // 3 // 8 * 8, n]
+    print(f"[case] n={n} scan_first={scan_first}", flush=True)
+    with Session(n, dynamic_scale=True, init_scale=1024.0, growth_interval=4, ring_bytes=24 << 20,
+                 timing=True) as sess:
+        load_state(sess, p0, w=ref.w)
+        steps = 0
+
+        def step(g, scan=False):
+            nonlocal steps
+            steps += 1
+            sess.backward_begin()
+            to_device_grad16(sess, g)
+            if scan:
+                sess.scan_grads(0, n)
+            sess.step(cfg.lr)
+            return oracle.adamw_step(ref, g, cfg)
+
+        def same(what):
+            assert sess.scaler() == (ref.t, ref.scale, ref.tracker), what
+            p, m, v, w = sess.state_to_host()
+            assert_bits_equal(p, ref.p, f"master after {what}")
+            assert_bits_equal(m, ref.m, f"exp_avg after {what}")
+            assert_bits_equal(v, ref.v, f"exp_avg_sq after {what}")
+            assert np.array_equal(w, ref.w), what
+
+        def window(what, **kw):
+            sess.begin_window(bounds, **kw)
+            recs = [step(good[s % 2]) for s in range(K)]
+            sess.drain()
+            got = sess.records()
+            for field in ("t", "skip", "scale_used"):
+                assert list(got[field]) == [r[field][0] for r in recs], (what, field)
+            assert list(got["window_step"]) == [1, 2, 3]
+            out = (np.empty(n, np.float32), np.empty(n, np.float32), np.empty(n, np.float32), np.empty(n, np.uint16))
+            meta = sess.restore(out=out)
+            assert (meta.t, meta.scale, meta.tracker) == (ref.t, ref.scale, ref.tracker), what
+            for a, b, name in zip(out, (ref.p, ref.m, ref.v, ref.w), ("master", "exp_avg", "exp_avg_sq", "w")):
+                assert_bits_equal(a, b, f"restored {name}, {what}")
+            same(what)
+
+        def plain(what):
+            for g in (good[0], inf, good[1]):
+                step(g, scan=scan_first)
+            same(what)
+
+        plain("plain steps")
+        window("the HOST_WAIT window", late_plan=1, timing=False)
+        plain("plain steps after the HOST_WAIT window")
+        window("the timed window", late_plan=2)
+        plain("plain steps after the timed window")
+        window("the untimed DEVICE_WAIT window", late_plan=2, timing=False)
+        plain("plain steps after the untimed window")
+    assert steps == 4 * 3 + 3 * K
