@@ -214,7 +214,7 @@ struct gockpt_ctx {
     int K = 0, s = 0;
     std::vector<int64_t> bounds;
     uint8_t* arena = nullptr;
-    uint8_t* arena_dev = nullptr;  // the pinned arena as a kernel sees it, or null
+    uint8_t* arena_dev = nullptr;  // the pinned arena as a kernel may write it, or null
     size_t arena_bytes = 0;
     gockpt_arena_layout lay{};
     std::vector<uint64_t> goff;
@@ -941,11 +941,18 @@ int gockpt_begin_window_ex(gockpt_ctx* c, int K, const int64_t* bounds, void* ho
     c->staged = !pinned;
     c->arena_dev = nullptr;
     if (pinned) {
+        // only if all of the arena lies in the one allocation: a copy checks
+        // its range against it, a kernel's stores would fault beyond it
         void* dev = nullptr;
-        if (hipHostGetDevicePointer(&dev, host_arena, 0) == hipSuccess)
-            c->arena_dev = static_cast<uint8_t*>(dev);
-        else
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipHostGetDevicePointer(&dev, host_arena, 0) == hipSuccess &&
+            hipMemGetAddressRange(&base, &size, dev) == hipSuccess) {
+            const size_t at = static_cast<size_t>(static_cast<uint8_t*>(dev) - static_cast<uint8_t*>(base));
+            if (at <= size && size - at >= lay.total) c->arena_dev = static_cast<uint8_t*>(dev);
+        } else {
             (void)hipGetLastError();
+        }
     }
     c->R = R;
     c->wait_policy = policy;
