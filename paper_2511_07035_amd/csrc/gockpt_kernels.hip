@@ -661,14 +661,15 @@ __global__ __launch_bounds__(kB) void fused_kernel(FusedArgs a) {
 // finds all partials there and updates its own tile.  The loss-scaler state
 // is read by every block and moved on by the last one to have read it.
 //
-// A partial is one 64-bit word, the sum (a double without its sign and its 11
-// last bits: 2^-41 relative, against 2^-24 for the prepass's fp32 squares)
-// and a tag of 12 bits, the step's epoch, which the last block moves on too.
-// A reader thus needs no order between the partial and a flag: no fence,
-// which on this chip would write back an XCD's L2.  Every step writes every
-// slot, so a slot that does not hold this epoch's tag holds the last one's.
-// A sum of squares in fp64 is finite exactly when every gradient is, so the
-// inf/NaN flag needs no bits of its own.
+// A partial is one 64-bit word: a double, and in the place of its sign, which
+// a sum of squares has no use for, the step's epoch modulo two, which the last
+// block moves on too.  A reader thus needs no order between the partial and a
+// flag: no fence, which on this chip would write back an XCD's L2.  Every step
+// writes every slot, so a slot whose tag is not this epoch's holds the last
+// step's partial: one bit tells them apart, and the sum keeps all of its bits
+// (the double in two words with 32 bits of epoch each: 10.1 us against 9.9 for
+// 1048579 elements).  A sum of squares in fp64 is finite exactly when every
+// gradient is, so the inf/NaN flag needs no bits of its own.
 // ---------------------------------------------------------------------------
 struct StepIn {  // what a block reads of the workspace
     StepState st;
@@ -734,16 +735,14 @@ __device__ __forceinline__ double tile_sumsq(const FusedArgs& a, int b, const u3
     return block_sum<kB>(acc, lds);
 }
 
-constexpr uint64_t kSlotTagMask = 0xFFF;
+constexpr uint64_t kSlotTag = uint64_t{1} << 63;
 
+__device__ __forceinline__ uint64_t slot_tag(uint32_t epoch) { return static_cast<uint64_t>(epoch) << 63; }
 __device__ __forceinline__ void publish(uint64_t* slot, uint32_t epoch, double x) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, x) << 1;
-    __hip_atomic_store(slot, (u & ~kSlotTagMask) | (epoch & kSlotTagMask), __ATOMIC_RELAXED,
+    __hip_atomic_store(slot, (__builtin_bit_cast(uint64_t, x) & ~kSlotTag) | slot_tag(epoch), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ double slot_value(uint64_t w) {
-    return __builtin_bit_cast(double, (w & ~kSlotTagMask) >> 1);
-}
+__device__ __forceinline__ double slot_value(uint64_t w) { return __builtin_bit_cast(double, w & ~kSlotTag); }
 
 // Counts this block in; true for the last of `tiles` blocks.  Two levels: one
 // counter for all of them took 12 ns a block, 3 us for 256.
@@ -865,14 +864,13 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
                     }
 #pragma unroll
                     for (int k = 0; k < kPer; ++k)
-                        if (tid + 64 * k < tiles && (word[k] & kSlotTagMask) != (epoch & kSlotTagMask))
-                            missing |= 1u << k;
+                        if (tid + 64 * k < tiles && (word[k] & kSlotTag) != slot_tag(epoch)) missing |= 1u << k;
                     if (__all(missing == 0u)) break;
                 }
                 if (__all(missing == 0u)) {
                     double x = 0.0;
 #pragma unroll
-                    for (int k = 0; k < kPer; ++k) x += slot_value(word[k] & ~kSlotTagMask);
+                    for (int k = 0; k < kPer; ++k) x += slot_value(word[k]);
                     x = wave_sum(x);
                     if (tid == 0) s_total = x, s_done = 1u;
                 } else {

@@ -211,3 +211,28 @@ def test_launch_forms_mixed_in_one_context(n, scan_first):
         window("the untimed DEVICE_WAIT window", late_plan=2, timing=False)
         plain("plain steps after the untimed window")
     assert steps == 4 * 3 + 3 * K
+
+
+@pytest.mark.parametrize("n", [1024, 65_536, 4 * ROW])
+@pytest.mark.parametrize("kw", [dict(), dict(late_plan=1)])
+def test_norm_keeps_every_bit_of_the_block_sums(n, kw):
+    """Squares that one double holds exactly, 1 and 2^-46 in every tile of up
+    to 4096 elements: their sum over one, 64 or 256 blocks is exact too, so
+    whatever carries the blocks' sums has to keep all of a double."""
+    import numpy as np
+
+    from gpu_util import to_device_grad16
+    from paper_2511_07035_amd import Session
+
+    bits = np.zeros(n, np.uint16)
+    bits[0::4096] = 0x3F80  # 1
+    bits[1023::4096] = 0x3400  # 2^-23
+    with Session(n, ring_bytes=1 << 20) as sess:
+        sess.begin_window([0, n], **kw)
+        sess.backward_begin()
+        to_device_grad16(sess, bits)
+        sess.step(1e-4)
+        sess.drain()
+        ones, small = len(bits[0::4096]), len(bits[1023::4096])
+        assert float(sess.records()["gnorm2"][0]) == ones + small * 2.0 ** -46
+        sess.abort_window()
