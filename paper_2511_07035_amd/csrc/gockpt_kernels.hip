@@ -8,7 +8,8 @@
 //                    run by the caller as soon as the backward has written
 //                    it: inf/NaN test and the sum of squares of the scaled
 //                    gradient in fp64 (the scale is applied at the finalize,
-//                    so the scan does not depend on the previous step).
+//                    so the scan does not depend on the previous step).  Also
+//                    the prepass of a small space whose step is not one launch.
 //   finalize_kernel  one block: reduces the partials (of the prepass or of the
 //                    bucket scans) in a fixed order, moves the loss scaler
 //                    and the step count, computes the step's scalars and

@@ -1329,9 +1329,15 @@ int gockpt_step(gockpt_ctx* c, float lr) {
                             !(scanned && c->scan_used > kAfterMaxParts) &&
                             !(in_window && c->ring_plan == GOCKPT_RING_HOST_WAIT && R);
     const int step_mode = scanned || (prepass && n > kStepMaxElems) ? kStepAfter : (prepass ? kStepJoint : kStepAlone);
+    const bool raw_prepass = prepass && n <= kStepMaxElems;
     if (prepass && !(one_launch && step_mode == kStepJoint)) {
+        // up to kStepMaxElems the squares are fp64 here too, as in the step that
+        // takes the sum itself: the norm does not depend on the launch form
         e = static_cast<hipError_t>(
-            launch_prepass(cfg.grad16, n, c->ws, c->pre_blocks, c->knobs.prepass_nt, cfg.grad_dtype, c->cs));
+            raw_prepass ? launch_scan(static_cast<const uint16_t*>(cfg.grad16), 0, n, c->ws + kWsPartialsOff,
+                                      c->pre_blocks, c->knobs.prepass_nt, cfg.grad_dtype, c->cs)
+                        : launch_prepass(cfg.grad16, n, c->ws, c->pre_blocks, c->knobs.prepass_nt, cfg.grad_dtype,
+                                         c->cs));
         if (e != hipSuccess) return c->hip_fail(e, "prepass launch");
     }
     for (const auto& se : c->scan_events)
@@ -1341,7 +1347,7 @@ int gockpt_step(gockpt_ctx* c, float lr) {
                                                                sizeof(Partial)
                                             : kWsPartialsOff);
     const int nparts = scanned ? c->scan_used : (prepass ? c->pre_blocks : 0);
-    fin.raw = scanned || (one_launch && step_mode == kStepJoint) ? 1 : 0;
+    fin.raw = scanned || raw_prepass ? 1 : 0;
     if (!one_launch) {
         e = static_cast<hipError_t>(
             launch_finalize(c->ws, parts, nparts, fin, c->cs));

@@ -91,8 +91,9 @@ def _run_window(n, K, bounds, *, seed, ring_bytes, copy_bytes=64 << 20, dynamic=
         assert list(recs["skip"]) == list(cap.records["skip"])
         assert list(recs["scale_used"]) == list(cap.records["scale_used"])
         assert list(recs["window_step"]) == list(range(1, K + 1))
-        # the device squares in fp32: a gradient above sqrt(FLT_MAX) makes the
-        # telemetry norm inf there, while the oracle sums in fp64
+        # above the one-launch step's size the prepass squares in fp32: a
+        # gradient above sqrt(FLT_MAX) makes the telemetry norm inf there, while
+        # the oracle sums in fp64
         dev_n, ora_n = recs["gnorm2"], cap.records["gnorm2"]
         if not grad_norm:
             assert np.all(dev_n == -1.0)

@@ -236,3 +236,46 @@ def test_norm_keeps_every_bit_of_the_block_sums(n, kw):
         ones, small = len(bits[0::4096]), len(bits[1023::4096])
         assert float(sess.records()["gnorm2"][0]) == ones + small * 2.0 ** -46
         sess.abort_window()
+
+
+FORMS = [dict(late_plan=2), dict(late_plan=1), dict(late_plan=2, timing=True), dict(late_plan=2, knob=("GOCKPT_QUADS", "2")),
+         dict(late_plan=2, found_inf=True)]
+
+
+@pytest.mark.parametrize("n", [50_003, 4 * ROW + 3, 4 * ROW + 4])
+def test_norm_of_a_huge_gradient_is_the_same_in_every_launch_form(n, monkeypatch):
+    """A gradient whose square leaves fp32: up to the one-launch step's size the
+    norm is the fp64 sum, above it the prepass's fp32 squares make it inf,
+    whether the step is one launch or several."""
+    import numpy as np
+    import torch
+
+    import synth
+    from gpu_util import to_device_grad16
+    from paper_2511_07035_amd import Session
+
+    g = synth.grads_cpu(n, 97, 1)
+    g[n // 2] = 0x60AD  # 1e20
+    x = (g.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    want = float(np.sum(x * x))
+    for form in FORMS:
+        kw = dict(form)
+        timing, knob, flag = kw.pop("timing", False), kw.pop("knob", None), kw.pop("found_inf", False)
+        fi = torch.zeros(1, dtype=torch.float32, device="cuda") if flag else None
+        with monkeypatch.context() as m:
+            if knob:
+                m.setenv(*knob)
+            sess = Session(n, ring_bytes=4 << 20, timing=timing, found_inf=fi)
+        with sess:
+            sess.begin_window([0, n], **kw)
+            sess.backward_begin()
+            to_device_grad16(sess, g)
+            sess.step(1e-4)
+            sess.drain()
+            rec = sess.records()[0]
+            sess.abort_window()
+        assert rec["skip"] == 0
+        if n <= 4 * ROW + 3:
+            assert abs(float(rec["gnorm2"]) - want) <= 1e-13 * want, form
+        else:
+            assert np.isinf(rec["gnorm2"]), form
