@@ -54,7 +54,8 @@ static_assert(sizeof(Partial) == 16, "Partial");
 struct alignas(64) StepSync {
     uint32_t epoch;
     uint32_t arrived;
-    uint32_t pad[14];
+    uint32_t helped;  // partials computed again for want of their block's, over the context's life
+    uint32_t pad[13];
 };
 static_assert(sizeof(StepSync) == 64, "StepSync");
 struct alignas(256) StepArrive {
@@ -192,6 +193,7 @@ struct Knobs {
     int fused_nt;     // nontemporal loads and stores of the state in the fused kernel
     int fused_block;  // fused kernel threads per block: kFusedBlock (default) or kFusedWideBlock
     bool defaults;    // none of the above asked for otherwise
+    int step_again;   // one-launch step: every block computes all partials again (GOCKPT_TEST_STEP_AGAIN)
 };
 
 // What the finalize of one step needs besides the partials.
@@ -230,7 +232,7 @@ int launch_fused(const FusedArgs& a, void* stream);
 // kStepMaxElems; the others: 1 <= n <= kAfterMaxElems, parts with kStepAfter.
 enum StepMode : int { kStepAlone = 0, kStepJoint = 1, kStepAfter = 2 };
 int launch_step(const FusedArgs& a, const FinalizeArgs& fin, int mode, void* workspace, const void* parts, int nparts,
-                void* stream);
+                int again, void* stream);
 Knobs default_knobs();
 
 }  // namespace gockpt

@@ -394,7 +394,7 @@ __global__ __launch_bounds__(kBlock) void init_kernel(uint8_t* __restrict__ ws, 
     for (size_t i = threadIdx.x; i < (kWsStepEnd - kWsSlotsOff) / 4; i += kBlock) words[i] = 0u;
     if (threadIdx.x != 0) return;
     *reinterpret_cast<DevScaler*>(ws + kWsScalerOff) = DevScaler{t, tracker, scale, 0, {}};
-    *reinterpret_cast<StepSync*>(ws + kWsSyncOff) = StepSync{1u, 0u, {}};
+    *reinterpret_cast<StepSync*>(ws + kWsSyncOff) = StepSync{1u, 0u, 0u, {}};
 }
 
 // ---------------------------------------------------------------------------
@@ -767,7 +767,7 @@ __device__ __forceinline__ bool arrive_last(StepSync* sync, StepArrive* lanes, i
 // alone 13.4 and 10.6, 22.1 and 20.7; behind 4 bucket scans 100 and 89.
 template <bool kHasW, int kB, int kQ, int kKind, int kMode>
 __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, uint8_t* __restrict__ ws,
-                                                  const Partial* __restrict__ parts, int nparts) {
+                                                  const Partial* __restrict__ parts, int nparts, int again) {
     constexpr uint32_t kTile = kB * kQ * 4;
     __shared__ StepScalars s_sc;
     __shared__ uint32_t s_epoch, s_found, s_done;
@@ -852,7 +852,7 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
     if constexpr (kMode == kStepJoint) {
         // the first wavefront polls, a lane for every 64th partial
         constexpr int kPer = kStepMaxTiles / 64;
-        for (;;) {
+        for (;; again = 0) {
             if (tid < 64) {
                 uint64_t word[kPer];
                 uint32_t missing = 0;  // bit k: this lane's k-th partial
@@ -867,6 +867,10 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
                     for (int k = 0; k < kPer; ++k)
                         if (tid + 64 * k < tiles && (word[k] & kSlotTag) != slot_tag(epoch)) missing |= 1u << k;
                     if (__all(missing == 0u)) break;
+                }
+                if (__builtin_expect(again, 0)) {
+#pragma unroll
+                    for (int k = 0; k < kPer; ++k) missing |= (tid + 64 * k < tiles ? 1u : 0u) << k;
                 }
                 if (__all(missing == 0u)) {
                     double x = 0.0;
@@ -885,7 +889,10 @@ __global__ __launch_bounds__(kB) void step_kernel(FusedArgs a, FinalizeArgs fa, 
             for (int b = 0; b < tiles; ++b) {
                 if (!s_missing[b]) continue;
                 const double x = tile_sumsq<kB, kQ, kKind>(a, b, nullptr, s_sum);
-                if (tid == 0) publish(slots + b, epoch, x);
+                if (tid == 0) {
+                    publish(slots + b, epoch, x);
+                    __hip_atomic_fetch_add(&sync->helped, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
                 __syncthreads();
             }
             __syncthreads();  // everyone has read s_done and s_missing
@@ -976,6 +983,7 @@ Knobs default_knobs() {
     k.prepass_nt = env_int("GOCKPT_PREPASS_NT", -1);
     k.fused_nt = env_int("GOCKPT_FUSED_NT", 1);
     k.fused_block = env_int("GOCKPT_FUSED_BLOCK", 0);
+    k.step_again = env_int("GOCKPT_TEST_STEP_AGAIN", 0);
     k.defaults = k.quads_per_thread == 1 && k.ring_nt == 1 && k.prepass_nt != 0 && k.fused_nt == 1 &&
                  k.fused_block != kFusedWideBlock;
     return k;
@@ -1076,7 +1084,7 @@ static int launch_fused_nt(const FusedArgs& a, hipStream_t s) {
 
 template <int kB, int kQ, int kKind, int kMode>
 static int launch_step_q(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, const Partial* parts, int nparts,
-                         hipStream_t s) {
+                         int again, hipStream_t s) {
     const int64_t per_block = static_cast<int64_t>(kB) * kQ * 4;
     int64_t tiles = (a.n / 4 * 4 + per_block - 1) / per_block;
     if (tiles < 1) tiles = 1;
@@ -1084,45 +1092,45 @@ static int launch_step_q(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws
     const unsigned grid = static_cast<unsigned>(tiles);
     if (a.w != nullptr)
         hipLaunchKernelGGL((step_kernel<true, kB, kQ, kKind, kMode>), dim3(grid), dim3(kB), 0, s, a, fa, ws, parts,
-                           nparts);
+                           nparts, again);
     else
         hipLaunchKernelGGL((step_kernel<false, kB, kQ, kKind, kMode>), dim3(grid), dim3(kB), 0, s, a, fa, ws, parts,
-                           nparts);
+                           nparts, again);
     return static_cast<int>(hipGetLastError());
 }
 
 template <int kKind, int kMode>
 static int launch_step_n(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws, const Partial* parts, int nparts,
-                         hipStream_t s) {
+                         int again, hipStream_t s) {
     const int64_t quads = a.n / 4, row = static_cast<int64_t>(kStepMaxTiles) * kBlock;
     // at most 256 tiles for the exchange, four partials a lane for the
     // wavefront that polls; beyond 256 tiles of one quad a lane, blocks of 512
     // threads (1.05e6 elements: two quads a lane 9% faster than 256 threads
     // and four)
-    if (quads <= row) return launch_step_q<kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, s);
-    if (quads <= 2 * row) return launch_step_q<2 * kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, s);
-    return launch_step_q<2 * kBlock, 2, kKind, kMode>(a, fa, ws, parts, nparts, s);
+    if (quads <= row) return launch_step_q<kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, again, s);
+    if (quads <= 2 * row) return launch_step_q<2 * kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, again, s);
+    return launch_step_q<2 * kBlock, 2, kKind, kMode>(a, fa, ws, parts, nparts, again, s);
 }
 
 template <int kKind>
 static int launch_step_kind(const FusedArgs& a, const FinalizeArgs& fa, int mode, uint8_t* ws, const Partial* parts,
-                            int nparts, hipStream_t s) {
+                            int nparts, int again, hipStream_t s) {
     switch (mode) {
-        case kStepJoint: return launch_step_n<kKind, kStepJoint>(a, fa, ws, parts, nparts, s);
-        case kStepAfter: return launch_step_n<kKind, kStepAfter>(a, fa, ws, parts, nparts, s);
-        default: return launch_step_n<kKind, kStepAlone>(a, fa, ws, parts, nparts, s);
+        case kStepJoint: return launch_step_n<kKind, kStepJoint>(a, fa, ws, parts, nparts, again, s);
+        case kStepAfter: return launch_step_n<kKind, kStepAfter>(a, fa, ws, parts, nparts, again, s);
+        default: return launch_step_n<kKind, kStepAlone>(a, fa, ws, parts, nparts, again, s);
     }
 }
 
 int launch_step(const FusedArgs& a, const FinalizeArgs& fin, int mode, void* workspace, const void* parts, int nparts,
-                void* stream) {
+                int again, void* stream) {
     hipStream_t s = static_cast<hipStream_t>(stream);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     const Partial* p = static_cast<const Partial*>(parts);
     if (a.n < 1 || a.n > (mode == kStepJoint ? kStepMaxElems : kAfterMaxElems))
         return static_cast<int>(hipErrorInvalidValue);
-    return a.grad_kind == kGradFP16 ? launch_step_kind<kGradFP16>(a, fin, mode, ws, p, nparts, s)
-                                    : launch_step_kind<kGradBF16>(a, fin, mode, ws, p, nparts, s);
+    return a.grad_kind == kGradFP16 ? launch_step_kind<kGradFP16>(a, fin, mode, ws, p, nparts, again, s)
+                                    : launch_step_kind<kGradBF16>(a, fin, mode, ws, p, nparts, again, s);
 }
 
 template <int kKind>

@@ -205,7 +205,7 @@ struct gockpt_ctx {
     hipStream_t cs = nullptr, xs = nullptr;
     uint8_t* ws = nullptr;
     int pre_blocks = 1;
-    Knobs knobs{1, 1, 1, 1, kFusedBlock, true};
+    Knobs knobs{1, 1, 1, 1, kFusedBlock, true, 0};
     size_t copy_bytes = GOCKPT_DEFAULT_COPY_BYTES;
     std::string err;
 
@@ -1500,7 +1500,8 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     }
     if (timed && (e = hipEventRecord(tm.upd0, c->cs)) != hipSuccess) return c->hip_fail(e, "event record");
     if (one_launch) {
-        if ((e = static_cast<hipError_t>(launch_step(a, fin, step_mode, c->ws, parts, nparts, c->cs))) != hipSuccess)
+        if ((e = static_cast<hipError_t>(launch_step(a, fin, step_mode, c->ws, parts, nparts,
+                                                     c->knobs.step_again, c->cs))) != hipSuccess)
             return c->hip_fail(e, "step launch");
     } else if (n > 0) {
         if ((e = static_cast<hipError_t>(launch_fused(a, c->cs))) != hipSuccess) return c->hip_fail(e, "fused launch");

@@ -46,6 +46,26 @@ def test_one_launch_step_options(kw):
     _run_window(n, 3, [0, 100_000, 200_008, n], seed=61, ring_bytes=1 << 20, **kw)
 
 
+@pytest.mark.parametrize("n", [1, 1027, 65_540, ROW + 1, 2 * ROW + 6, 4 * ROW + 3])
+@pytest.mark.parametrize("grad_dtype", ["bf16", "fp16"])
+def test_blocks_compute_the_partials_they_miss(n, grad_dtype, monkeypatch):
+    """Every block of the one-launch step takes all partials for missing once
+    and computes them itself: counted in the workspace (the third sync word, 64
+    bytes in), with a skipped step, and every bit the oracle's."""
+    import torch
+
+    monkeypatch.setenv("GOCKPT_TEST_STEP_AGAIN", "1")
+    K = 3 if n >= 64 else 1
+    bounds = [0] + [n * k // K // 8 * 8 for k in range(1, K)] + [n]
+    sess, stats, _ = _run_window(n, K, bounds, seed=n % 83, ring_bytes=1 << 20, dynamic=True,
+                                 inf_steps=(2,) if K > 1 else (), late_plan=2, grad_dtype=grad_dtype)
+    assert stats.skipped == (1 if K > 1 else 0)
+    tile = 1024 if n // 4 <= ROW // 4 else (2048 if n // 4 <= 2 * ROW // 4 else 4096)
+    tiles = max(1, -(-(n // 4 * 4) // tile))
+    helped = int(sess.workspace[64:128].view(torch.int32)[2])
+    assert helped >= K * tiles * tiles
+
+
 def test_one_launch_step_beside_a_full_device():
     """The blocks of a one-launch step need not run together: with another
     kernel on all but a few of the device's places, those that run compute the
@@ -54,7 +74,8 @@ def test_one_launch_step_beside_a_full_device():
     one of the places left is the device's choice (its shader engines take
     blocks in turn, and both streams may share a hardware queue), so the bits
     are checked for every number of places, and that the step ran beside the
-    other kernel for those where it could."""
+    other kernel for those where it could.  (That blocks compute each other's
+    partials at all does not hang on the device's choice: the test above.)"""
     import time
 
     import numpy as np
@@ -214,16 +235,20 @@ def test_launch_forms_mixed_in_one_context(n, scan_first):
 
 
 @pytest.mark.parametrize("n", [1024, 65_536, 4 * ROW])
-@pytest.mark.parametrize("kw", [dict(), dict(late_plan=1)])
-def test_norm_keeps_every_bit_of_the_block_sums(n, kw):
+@pytest.mark.parametrize("kw", [dict(), dict(late_plan=1), dict(again="1")])
+def test_norm_keeps_every_bit_of_the_block_sums(n, kw, monkeypatch):
     """Squares that one double holds exactly, 1 and 2^-46 in every tile of up
     to 4096 elements: their sum over one, 64 or 256 blocks is exact too, so
-    whatever carries the blocks' sums has to keep all of a double."""
+    whatever carries the blocks' sums has to keep all of a double -- also where
+    the blocks compute each other's."""
     import numpy as np
 
     from gpu_util import to_device_grad16
     from paper_2511_07035_amd import Session
 
+    kw = dict(kw)
+    if "again" in kw:
+        monkeypatch.setenv("GOCKPT_TEST_STEP_AGAIN", kw.pop("again"))
     bits = np.zeros(n, np.uint16)
     bits[0::4096] = 0x3F80  # 1
     bits[1023::4096] = 0x3400  # 2^-23
