@@ -1,8 +1,10 @@
 """The update kernel at the sizes where its launch shape changes, against the
 oracle, bit for bit: around the last size of the latency-bound shape (256
-threads a block) and the first of the bandwidth-bound one (one-wavefront
-blocks of 256 elements under a residency limit), with ragged ends, parts that
-begin inside a tile, a ring that wraps and spills, and a skipped step."""
+threads a block, or one launch for the whole step) and the first of the
+bandwidth-bound one (one-wavefront blocks of 256 elements under a residency
+limit), with ragged ends, parts that begin inside a tile, a ring that wraps and
+spills, and a skipped step; the one-launch step in each of its forms, beside
+the separate kernels in one context; and a small window step's copies."""
 import pytest
 
 from test_gpu_parity import _run_window
@@ -12,11 +14,15 @@ pytestmark = pytest.mark.gpu
 SHAPE_EDGE = 2 * 256 * 32 * 256  # elements: two rounds of all wave slots, a quad a lane
 
 
-@pytest.mark.parametrize("n", [SHAPE_EDGE, SHAPE_EDGE + 1, SHAPE_EDGE + 256 + 7, SHAPE_EDGE + 2 * 256 - 4])
-def test_update_shapes_same_bits(n):
+@pytest.mark.parametrize("n", [SHAPE_EDGE - 5, SHAPE_EDGE, SHAPE_EDGE + 1, SHAPE_EDGE + 256 + 7,
+                               SHAPE_EDGE + 2 * 256 - 4])
+@pytest.mark.parametrize("late_plan", [1, 2])
+def test_update_shapes_same_bits(n, late_plan):
+    """late_plan 1 (HOST_WAIT) keeps the update a launch of its own on both
+    sides of the edge; with 2 the step up to the edge is step_kernel's."""
     bounds = [0, 1_000_008, 2_097_152 + 248, n]
     _, stats, _ = _run_window(n, 3, bounds, seed=n % 97, ring_bytes=12 << 20, copy_bytes=4 << 20, dynamic=True,
-                              inf_steps=(3,), late_plan=2)
+                              inf_steps=(3,), late_plan=late_plan)
     assert stats.bytes_spilled > 0 and stats.bytes_ring > 0 and stats.skipped == 1
 
 
