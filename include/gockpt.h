@@ -263,7 +263,11 @@ typedef struct {
                              looked (check_overflow = 0, grad_norm_off = 1) */
     int32_t window_step;  /* s in 1..K inside a window, 0 otherwise */
     double gnorm2;        /* sum of squares of the unscaled gradients; -1
-                             with grad_norm_off */
+                             with grad_norm_off.  Squares in fp64 up to
+                             1048579 elements and in bucket scans; in fp32
+                             otherwise, where a gradient above 1.8e19 makes it
+                             inf.  Its last bits depend on the order of the
+                             sum, which differs by launch form. */
     float step_size;      /* scalars the device used (see the contract) */
     float sqrt_bc2;
     float decay;

@@ -22,11 +22,12 @@ constexpr int kVec = 8;                 // elements per thread per group
 // 1721).  The prepass fills the device: one, two, four or eight loads are
 // within 1% from 8.4e6 elements on; below, two were 3% faster (2.1e6: 15.0,
 // 14.5, 15.0, 16.4 us a step).
-constexpr int64_t kCachedGradBytes = 512 << 20;  // read with the nontemporal hint above this
 constexpr int kPrepassAhead = 2;
 constexpr int kScanAhead = 4;
+// Above this many gradient bytes the prepass and the scans read with the
+// nontemporal hint (see create_ctx).
+constexpr int64_t kCachedGradBytes = 512 << 20;
 constexpr int kPrepassMaxBlocks = 2048; // partial sums slots
-constexpr int kFinalizeThreads = 256;
 constexpr int kScanSlots = 8192;        // partials of the bucket scans of one step
 constexpr int kScanMaxBlocks = 256;     // blocks of a bucket scan beside the backward (one per compute unit)
 
@@ -161,7 +162,8 @@ struct FusedArgs {
     int32_t quads_per_thread;       // 1, 2 or 4 quads (4 elements) per thread
     int32_t grad_kind;              // kGradBF16 or kGradFP16
     int32_t nt;                     // nontemporal state loads and stores
-    int32_t block;                  // threads per block: kFusedBlock or kFusedWideBlock (one quad per lane)
+    int32_t block;                  // kFusedWideBlock (one quad per lane), or kFusedBlock: kBlock threads a block up
+                                    // to 4.2e6 elements, kFusedBlock above (launch_fused_nt)
     PackPlan pack;
 };
 

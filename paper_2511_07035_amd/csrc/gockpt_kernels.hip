@@ -31,9 +31,12 @@
 // (fp32), working weights (bf16) and gradients (bf16 or fp16), each
 // contiguous over the flat parameter space.  The fused kernel gives each lane
 // one quad of 4 consecutive elements per tile (see fused_kernel); the prepass
-// reads 8 gradients per lane per iteration.  The kernels are HBM-bound (28
-// bytes per element per step plus the pack), so no LDS and no matrix cores:
-// the work is elementwise.
+// reads 8 gradients per lane per iteration.  The large kernels are HBM-bound
+// (28 bytes per element per step plus the pack) and the work is elementwise:
+// no matrix cores, and LDS only where blocks reduce a sum, in step_kernel to
+// hand the step's scalars and the exchange's result around, and in
+// fused_kernel as an allocation that limits how many blocks share a compute
+// unit.
 
 #include <hip/hip_runtime.h>
 
@@ -66,10 +69,12 @@ __device__ __forceinline__ T ld_stream(const T* p) {
 // A store of 8 or 16 bytes at a byte offset into a tile whose base is the same
 // for the whole block.  kThrough: beside the hint it is written through the L2
 // (sc1), so that no line waits there for its turn.  For the bandwidth-bound
-// shape; us a step with the hint alone and written through: 16.8e6 elements
-// 77.9 and 76.5, 33.6e6 151.5 and 149.5, 124e6 573 and 562, 350e6 1660 and
-// 1635, 1.63e9 the same within 0.5%.  Not for 2.1e6 elements, whose lines the
-// next step still finds in the L2: 17.1 and 17.9.
+// shape, the update from 4.2e6 elements on; us a step with the hint alone and
+// written through: 5.0e6 elements 31.2 and 31.2, 6.3e6 35.5 and 35.4, 8.4e6
+// 46.2 and 45.7, 10.5e6 55.8 and 54.9, 12.6e6 65.2 and 63.8, 16.8e6 77.9 and
+// 76.5, 33.6e6 151.5 and 149.5, 124e6 573 and 562, 350e6 1660 and 1635, 1.63e9
+// the same within 0.5%.  Not for 2.1e6 elements, whose lines the next step
+// still finds in the L2: 17.1 and 17.9.
 template <bool kNT, bool kThrough, uint32_t kTileBytes, class T>
 __device__ __forceinline__ void st_tile(void* base, uint32_t off, T v) {
     static_assert(sizeof(T) == 16 || sizeof(T) == 8, "8 or 16 bytes");
@@ -377,7 +382,8 @@ __global__ __launch_bounds__(kBlock) void scan_kernel(const uint16_t* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// Finalize on its own (bucket scans, a caller's flag, or no prepass at all).
+// Finalize on its own: above kAfterMaxElems, in timed and HOST_WAIT windows,
+// with a launch knob, and behind more than kAfterMaxParts scan partials.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void finalize_kernel(uint8_t* __restrict__ ws, const Partial* __restrict__ parts,
                                                           int nparts, FinalizeArgs fa) {
@@ -760,7 +766,8 @@ __device__ __forceinline__ bool arrive_last(StepSync* sync, StepArrive* lanes, i
 // norm) and takes it itself.  kStepAfter: a prepass or bucket scans before it
 // have left their partials (at most kAfterMaxParts), which every block reduces
 // for itself instead of waiting for a finalize launch; kStepAlone: nothing is
-// summed.  These two exchange nothing, so they may have more blocks than the
+// summed.  In these two no block waits for another's sum (they only count
+// their arrivals, as kStepJoint does), so they may have more blocks than the
 // device has places, and go up to kAfterMaxElems, where the separate kernels'
 // shape changes.  us a step with a finalize launch and without: behind a
 // prepass 2.1e6 elements 17.1 and 14.2, 4.2e6 27.6 and 25.4 (1.05e6 the same);
@@ -1055,7 +1062,12 @@ static int launch_fused_q(const FusedArgs& a, hipStream_t s) {
     //   1.63e9 elements   8454 | 7984 | 7710 | 7626 | 7710 | 7695 | 7862 | 8018
     //   1.24e8 elements    662 |  628 |  609 |  591 |  588 |  612 |  597 |  625
     //   1.68e7 elements   85.7 | 86.0 | 82.6 | 80.8 | 80.7 | 81.3 | 82.1 | 86.1
-    // Two or four quads a lane were no better at any of them.
+    // Two or four quads a lane (on request) were no better at any of them, and
+    // take no limit.  Beside matrix products on another stream, whose blocks
+    // want LDS too (ms for all steps | all products, this limit; no limit;
+    // 256-thread blocks): 30 steps of 124e6 and 40 products of 4096^3 19.9 |
+    // 12.4; 21.3 | 13.2; 23.1 | 14.0, and 6 of 8192^3 20.9 | 5.8; 22.0 | 5.9;
+    // 24.3 | 6.0, and 300 of 2048^3 22.7 | 12.4; 23.6 | 17.2; 26.1 | 26.5.
     const unsigned lds = kB == kFusedBlock && kQ == 1 ? kFusedLds : 0u;
     if (a.w != nullptr)
         hipLaunchKernelGGL((fused_kernel<true, kQ, kKind, kNT, kB>), dim3(grid), dim3(kB), lds, s, a);

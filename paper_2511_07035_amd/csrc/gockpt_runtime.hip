@@ -727,11 +727,15 @@ int create_ctx(const gockpt_config* cfg, uint8_t* ws, bool with_ctrl, gockpt_ctx
     // 16-wavefront one (which cannot start on a compute unit another kernel
     // partly holds, so it slows down badly beside concurrent kernels)
     if (c->knobs.fused_block != kFusedWideBlock) c->knobs.fused_block = kFusedBlock;
-    // gradients that the last-level cache (256 MB) largely holds are read by
-    // the prepass and the scans without the nontemporal hint: the update then
-    // finds them there (us a step with and without it: 33.6e6 elements 157 and
-    // 151, 66e6 307 and 297, 124e6 574 and 555; 250e6 1157 and 1126..1166,
-    // from there on the same within 1%)
+    // without the nontemporal hint the prepass and the scans leave the
+    // gradients they read last in the last-level cache (256 MB), where the
+    // update finds them.  That saves about 20 us however large the space is,
+    // until what they displace costs as much (us a step with and without the
+    // hint: 20e6 elements 97 and 94, 60e6 277 and 264, 134e6 616 and 593, 190e6
+    // 868 and 842, 250e6 1133 and 1109, 300e6 1357 and 1335, 400e6 1809 and
+    // 1790, 500e6 2294 and 2283, 1e9 4506 and 4512, 1.6e9 7449 and 7488; eight
+    // bucket scans 124e6 686 and 659, 250e6 1271 and 1244, 500e6 2481 and
+    // 2455).  The line lies below the sizes where that is under 2%.
     if (c->knobs.prepass_nt < 0) c->knobs.prepass_nt = 2 * cfg->n > kCachedGradBytes ? 1 : 0;
     if (const char* f = getenv("GOCKPT_TEST_FAIL_COPY")) c->fail_copy_at = atoll(f);
     auto env_on = [](const char* name) {
