@@ -1062,6 +1062,12 @@ static int launch_fused_q(const FusedArgs& a, hipStream_t s) {
     //   1.63e9 elements   8454 | 7984 | 7710 | 7626 | 7710 | 7695 | 7862 | 8018
     //   1.24e8 elements    662 |  628 |  609 |  591 |  588 |  612 |  597 |  625
     //   1.68e7 elements   85.7 | 86.0 | 82.6 | 80.8 | 80.7 | 81.3 | 82.1 | 86.1
+    // What it costs: blocks start at 0.21 ns each, so a skipped step, whose
+    // blocks do nothing, takes 106 us for 1.24e8 elements and 1.08 ms for 1.3e9
+    // against 43 and 0.40 with 256-thread blocks.  Fewer, larger ones lose more
+    // on every step that is not skipped (1.3e9: 5.83 ms; two quads a lane at
+    // its best residency 6.02; 128 threads, 6 blocks a compute unit 6.25; 256
+    // threads, 3 blocks 6.45; four tiles a block in turn 6.48).
     // Two or four quads a lane (on request) were no better at any of them, and
     // take no limit.  Beside matrix products on another stream, whose blocks
     // want LDS too (ms for all steps | all products, this limit; no limit;

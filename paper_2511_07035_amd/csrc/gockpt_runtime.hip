@@ -1326,6 +1326,9 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     // the gradients too, as far as its blocks hold their tiles in registers
     // (there it is still the faster one, 9.8 us against 11.1); up to
     // kAfterMaxElems it reduces the partials of the prepass or the scans.
+    // A skipped step pays for it above 2e6 elements, where it has loaded and
+    // computed what it then drops (4.2e6: 17.6 us, 8.9 with three launches, for
+    // the 2.2 us that every other step saves).
     // Not where the finalize has to end before the update is launched: the
     // HOST_WAIT plan reads its decision, and timing events stand around both.
     // The launch-shape knobs belong to the separate kernels.
@@ -1502,12 +1505,25 @@ int gockpt_step(gockpt_ctx* c, float lr) {
             }
         }
     }
+    if (skipped) {
+        // the launch covers what the step packs: elsewhere a skipped step's
+        // blocks have nothing to do, but starting them takes 0.21 ns each
+        // (1.3e9 elements, parts of 163e6: 1.72 ms with all of them, 0.65 with
+        // these)
+        int64_t end = pk.cb;
+        for (int k = 0; k < 3; ++k) end = pk.s_end[k] > end ? pk.s_end[k] : end;
+        a.p += pk.cb, a.m += pk.cb, a.v += pk.cb, a.g += pk.cb;
+        if (a.w != nullptr) a.w += pk.cb;
+        a.n = end - pk.cb;
+        for (int k = 0; k < 3; ++k) pk.s_end[k] -= pk.cb;
+        pk.cb = 0;
+    }
     if (timed && (e = hipEventRecord(tm.upd0, c->cs)) != hipSuccess) return c->hip_fail(e, "event record");
     if (one_launch) {
         if ((e = static_cast<hipError_t>(launch_step(a, fin, step_mode, c->ws, parts, nparts,
                                                      c->knobs.step_again, c->cs))) != hipSuccess)
             return c->hip_fail(e, "step launch");
-    } else if (n > 0) {
+    } else if (a.n > 0) {
         if ((e = static_cast<hipError_t>(launch_fused(a, c->cs))) != hipSuccess) return c->hip_fail(e, "fused launch");
     }
     if (timed && (e = hipEventRecord(tm.upd1, c->cs)) != hipSuccess) return c->hip_fail(e, "event record");

@@ -9,8 +9,13 @@
 static char* pin_at;
 static size_t pin_len;
 static long n_launch, n_memcpy;
+static unsigned last_grid;
+static void* page;
+static size_t page_len;
 
 void fake_set_pinned(void* at, size_t len) { pin_at = at, pin_len = len; }
+void fake_fill_page(int byte) { memset(page, byte, page_len); } /* the newest hipHostMalloc */
+unsigned fake_last_grid(void) { return last_grid; }
 long fake_launches(void) { return n_launch; }
 long fake_memcpys(void) { return n_memcpy; }
 
@@ -26,7 +31,9 @@ hipError_t hipEventSynchronize(hipEvent_t e) { return (void)e, hipSuccess; }
 hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
 const char* hipGetErrorString(hipError_t e) { return e == hipSuccess ? "success" : "error"; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t hipHostMalloc(void** p, size_t n, unsigned f) { return (void)f, *p = calloc(1, n), hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned f) {
+    return (void)f, *p = page = calloc(1, n), page_len = n, hipSuccess;
+}
 hipError_t hipHostFree(void* p) { return free(p), hipSuccess; }
 hipError_t hipHostGetDevicePointer(void** d, void* h, unsigned f) { return (void)f, *d = h, hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { return (void)s, hipSuccess; }
@@ -46,9 +53,12 @@ hipError_t hipMemGetAddressRange(hipDeviceptr_t* base, size_t* size, hipDevicept
     return *base = pin_at, *size = pin_len, hipSuccess;
 }
 hipError_t hipLaunchKernel(const void* f, dim3 g, dim3 b, void** a, size_t l, hipStream_t s) {
-    return (void)f, (void)g, (void)b, (void)a, (void)l, (void)s, n_launch++, hipSuccess;
+    return (void)f, (void)b, (void)a, (void)l, (void)s, last_grid = g.x, n_launch++, hipSuccess;
 }
-hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t l, hipStream_t s) { return (void)g, (void)b, (void)l, (void)s, hipSuccess; }
+static dim3 conf_grid, conf_block;
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t l, hipStream_t s) {
+    return (void)l, (void)s, conf_grid = g, conf_block = b, hipSuccess;
+}
 hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* l, hipStream_t* s) {
-    return memset(g, 0, sizeof *g), memset(b, 0, sizeof *b), *l = 0, *s = NULL, hipSuccess;
+    return *g = conf_grid, *b = conf_block, *l = 0, *s = NULL, hipSuccess;
 }
