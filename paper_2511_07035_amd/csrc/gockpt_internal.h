@@ -66,7 +66,16 @@ constexpr int kStepArriveLanes = 16;
 constexpr int kStepMaxTiles = 256;  // four partials a lane of the wavefront that reads them
 static_assert(kStepMaxTiles % 64 == 0, "whole rows of a wavefront");
 constexpr int64_t kStepMaxElems = int64_t{kStepMaxTiles} * 512 * 2 * 4 + 3;  // two quads a lane, and the tail
-// Steps in one launch behind a prepass or bucket scans, or with nothing to sum.
+// Steps in one launch behind a prepass, or with nothing to sum: where the whole
+// step could be one, and from kAfterMinElems to kAfterMaxElems.  Between them
+// there are more blocks than compute units and too few to even that out, and
+// the separate kernels' smaller ones are as fast or faster (us a step separate
+// and in one launch, each at its best shape: behind a prepass 1.05e6 elements
+// 10.6..12.1 and 11.9, 1.2e6 11.6..12.3 and 12.4, 1.35e6 13.2 and 12.5, 1.5e6
+// 13.6 and 12.6; alone 8.1 and 8.7, 8.7 and 9.4, 10.3 and 9.5, 10.9 and 9.6).
+// Behind bucket scans one launch is the faster one there too (13.0 and 11.8,
+// 13.2 and 12.2 for 1.05e6 and 1.2e6).
+constexpr int64_t kAfterMinElems = 5 << 18;
 constexpr int64_t kAfterMaxElems = int64_t{1} << 22;
 constexpr int kAfterMaxParts = 512;  // partials every block then reduces: 8 KiB from the L2
 constexpr int kStepHelpSpins = 32;  // polls (0.5 to 1 us each) before a block computes the partials it misses

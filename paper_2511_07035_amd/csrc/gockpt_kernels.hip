@@ -1124,9 +1124,13 @@ static int launch_step_n(const FusedArgs& a, const FinalizeArgs& fa, uint8_t* ws
     // at most 256 tiles for the exchange, four partials a lane for the
     // wavefront that polls; beyond 256 tiles of one quad a lane, blocks of 512
     // threads (1.05e6 elements: two quads a lane 9% faster than 256 threads
-    // and four)
+    // and four).  Without the exchange one quad a lane again as long as three
+    // blocks a compute unit hold all (us a step behind a prepass, one quad a
+    // lane and two: 1.35e6 elements 12.5 and 13.2, 1.5e6 12.6 and 13.0, 1.65e6
+    // 14.5 and 13.4).
     if (quads <= row) return launch_step_q<kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, again, s);
-    if (quads <= 2 * row) return launch_step_q<2 * kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, again, s);
+    if (quads <= 2 * row || (kMode != kStepJoint && quads > 4 * row && quads <= 6 * row))
+        return launch_step_q<2 * kBlock, 1, kKind, kMode>(a, fa, ws, parts, nparts, again, s);
     return launch_step_q<2 * kBlock, 2, kKind, kMode>(a, fa, ws, parts, nparts, again, s);
 }
 

@@ -1324,8 +1324,9 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     // Small spaces end the step in the launch that updates (step_kernel),
     // queued where the update would be: up to kStepMaxElems it tests and sums
     // the gradients too, as far as its blocks hold their tiles in registers
-    // (there it is still the faster one, 9.8 us against 11.1); up to
-    // kAfterMaxElems it reduces the partials of the prepass or the scans.
+    // (there it is still the faster one, 9.8 us against 11.1); from
+    // kAfterMinElems, or behind scans, up to kAfterMaxElems it reduces the
+    // partials of the prepass or the scans.
     // A skipped step pays for it above 2e6 elements, where it has loaded and
     // computed what it then drops (4.2e6: 17.6 us, 8.9 with three launches, for
     // the 2.2 us that every other step saves).
@@ -1333,6 +1334,7 @@ int gockpt_step(gockpt_ctx* c, float lr) {
     // HOST_WAIT plan reads its decision, and timing events stand around both.
     // The launch-shape knobs belong to the separate kernels.
     const bool one_launch = n > 0 && n <= kAfterMaxElems && !timed && c->knobs.defaults &&
+                            (scanned || n <= kStepMaxElems || n >= kAfterMinElems) &&
                             !(scanned && c->scan_used > kAfterMaxParts) &&
                             !(in_window && c->ring_plan == GOCKPT_RING_HOST_WAIT && R);
     const int step_mode = scanned || (prepass && n > kStepMaxElems) ? kStepAfter : (prepass ? kStepJoint : kStepAlone);

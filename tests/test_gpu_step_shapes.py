@@ -143,20 +143,21 @@ def test_small_step_copies_in_one_kernel(case):
 
 @pytest.mark.parametrize("kw", [dict(), dict(grad_dtype="fp16"), dict(grad_norm=False, found_inf=[0.0, 1.0, 0.0]),
                                 dict(check_overflow=False, grad_norm=False, with_weight=False)])
-def test_step_behind_a_prepass_or_alone(kw):
-    """Between the one-launch sizes and 2^22 the launch that updates also
-    reduces the prepass's partials, or has nothing to reduce."""
-    n = 2_000_003
+@pytest.mark.parametrize("n", [5 * ROW - 1, 5 * ROW, 6 * ROW + 3, 6 * ROW + 4, 2_000_003])
+def test_step_behind_a_prepass_or_alone(kw, n):
+    """From 5 * 2^18 elements to 2^22 the launch that updates also reduces the
+    prepass's partials, or has nothing to reduce; its shape changes at 6 * 2^18.
+    Just below, the kernels are separate."""
     inf = dict(dynamic=True, inf_steps=(3,)) if kw.get("check_overflow", True) and "found_inf" not in kw else {}
-    _, stats, _ = _run_window(n, 3, [0, 600_000, 1_400_008, n], seed=67, ring_bytes=6 << 20, late_plan=2, **inf, **kw)
+    _, stats, _ = _run_window(n, 3, [0, 600_000, n * 7 // 10 // 8 * 8, n], seed=67, ring_bytes=6 << 20, late_plan=2, **inf, **kw)
     assert stats.skipped == (1 if inf or "found_inf" in kw else 0)
 
 
-@pytest.mark.parametrize("buckets", [1, 7, 512, 600])
-def test_step_behind_bucket_scans(buckets):
+@pytest.mark.parametrize("buckets,n", [(1, 700_003), (7, 700_003), (512, 700_003), (600, 700_003),
+                                       (3, 1_200_005)])
+def test_step_behind_bucket_scans(buckets, n):
     """Up to 512 partials of bucket scans are reduced by the launch that
     updates, more by a finalize of their own; with a skipped step."""
-    n = 700_003
     ends = [n * k // buckets // 8 * 8 for k in range(buckets)] + [n]
     _, stats, _ = _run_window(n, 4, [0, 200_000, 400_000, 600_000, n], seed=73, ring_bytes=4 << 20, dynamic=True,
                               inf_steps=(3,), scan_buckets=ends, per_step=False)
