@@ -26,6 +26,7 @@
 #include <atomic>
 #include <chrono>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -242,7 +243,10 @@ bool parallel_pieces(size_t count, int nthreads, F body) {
     if (nthreads <= 0) nthreads = 16;
     if (static_cast<size_t>(nthreads) > count) nthreads = count ? static_cast<int>(count) : 1;
     std::vector<std::thread> pool;
-    for (int i = 1; i < nthreads; ++i) pool.emplace_back(worker);
+    try {
+        for (int i = 1; i < nthreads; ++i) pool.emplace_back(worker);
+    } catch (const std::system_error&) {  // no more threads to be had: those there are do it
+    }
     worker();
     for (auto& t : pool) t.join();
     return ok.load();

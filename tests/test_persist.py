@@ -188,3 +188,35 @@ def test_checksum_of_a_piece_read_in_blocks(tmp_path, n):
                 gockpt_read_checkpoint(d, n)
             flip()
         gockpt_read_checkpoint(d, n)
+
+
+def test_reading_goes_on_with_the_threads_there_are(tmp_path):
+    """A file of three pieces is read by as many threads as it has blocks; where
+    the process cannot start them all (here its address space is nearly used
+    up), the call reads with those it got instead of ending the process."""
+    import subprocess
+    import sys
+    n = 2_000_003
+    p, m, v = (np.random.default_rng(k).standard_normal(n, dtype=np.float32) for k in range(3))
+    d = str(tmp_path / "ck")
+    gockpt_write_checkpoint(d, p, m, v)
+    script = f"""
+import ctypes, resource, sys
+import numpy as np
+import paper_2511_07035_amd as g
+n, d = {n}, {d!r}
+L = g.lib()
+out = [np.ones(n, np.float32) for _ in range(3)]
+args = (d.encode(), n, *(a.ctypes.data for a in out), None, 16, None)
+assert L.gockpt_read_checkpoint(*args) == 0  # what the first call maps is there
+vm = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()
+for a in out:
+    a.fill(0.0)
+resource.setrlimit(resource.RLIMIT_AS, (vm + (40 << 20),) * 2)  # four stacks of 8 MiB
+assert L.gockpt_read_checkpoint(*args) == 0
+print([float(a.sum(dtype=np.float64)) for a in out], flush=True)
+"""
+    r = subprocess.run([sys.executable, "-c", script], capture_output=True, text=True, timeout=120,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+    assert eval(r.stdout) == [float(a.sum(dtype=np.float64)) for a in (p, m, v)]
