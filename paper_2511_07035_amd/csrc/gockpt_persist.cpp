@@ -61,7 +61,7 @@ uint32_t crc32c(const uint8_t* p, uint64_t len) {
 // CRCs of a message's blocks make the CRC of the whole.  Appending len bytes
 // to a message multiplies the polynomial its CRC stands for by x^(8 len)
 // modulo the generator; bit 31 of a CRC is the coefficient of x^0.
-uint32_t mul_mod(uint32_t a, uint32_t b) {
+constexpr uint32_t mul_mod(uint32_t a, uint32_t b) {
     uint32_t r = 0;
     for (int k = 0; k < 32; ++k) {
         if (a & (0x80000000u >> k)) r ^= b;
@@ -70,7 +70,7 @@ uint32_t mul_mod(uint32_t a, uint32_t b) {
     return r;
 }
 
-uint32_t x_pow_bytes(uint64_t len) {
+constexpr uint32_t x_pow_bytes(uint64_t len) {
     uint32_t r = 0x80000000u, base = 0x00800000u;  // 1 and x^8
     for (; len > 0; len >>= 1) {
         if (len & 1u) r = mul_mod(r, base);
@@ -526,7 +526,7 @@ int gockpt_read_checkpoint(const char* dir, int64_t n, float* master, float* exp
     if (!ok)
         return fail(GOCKPT_EFAILED, std::string("read_checkpoint: reading data.bin: ") +
                                         (io_errno.load() ? strerror(io_errno.load()) : "short read"));
-    const uint32_t whole = x_pow_bytes(kReadBlock);
+    constexpr uint32_t whole = x_pow_bytes(kReadBlock);
     for (size_t k = 0; k < blocks.size();) {
         const size_t piece = blocks[k].piece;
         const Piece& p = L.pieces[piece];
